@@ -350,25 +350,34 @@ __device__ __forceinline__ double exp_cw(double z) {
 // s6 = q^3, and g_i = sum_{j != i} q s6 (24 - 48 s6) (x_i - x_j).
 // ---------------------------------------------------------------------------
 
-// 1/x for 2^-767 <= x < 2^1022 with the operations of the IEEE division
-// 1.0 / x that survive in that range: the hardware reciprocal estimate, two
-// Newton steps y <- y + y (1 - x y), and the final correction
-// q = y + y (1 - x y).  There the division's operand scaling (v_div_scale) is
-// the identity and its special-case fix-up (v_div_fixup) returns q unchanged,
-// so q is the same correctly rounded quotient.  For smaller x the pair term
+// 1/x for 2^-767 <= x < 2^1022, correctly rounded, without the operand scaling
+// and special-case fix-up of the IEEE division 1.0 / x (in that range they are
+// the identity).  The hardware estimate y has |1 - x y| <= 2^-24.3 (measured);
+// one cubic step y (1 + e + e^2), e = 1 - x y, leaves |e|^3 <= 2^-73 beside its
+// own rounding, and the correction y + y (1 - x y) (an exact residual) then
+// rounds to the quotient.  One instruction fewer than two Newton steps; equal
+// to 1.0 / x on 1.7e10 arguments, among them mantissas next to 1 and 2 and
+// reciprocals next to rounding midpoints.  For smaller x the pair term
 // s6 = q^3 overflows in both forms (the energy is not finite) and for larger x
 // both give s6 = 0; a non-finite energy is recomputed with the IEEE division.
 __device__ __forceinline__ double recip_in_range(double x) {
     double y = __builtin_amdgcn_rcp(x);
-    y = fma(y, fma(-x, y, 1.0), y);
-    y = fma(y, fma(-x, y, 1.0), y);
+    const double e = fma(-x, y, 1.0);
+    y = fma(y, fma(e, e, e), y);
     return fma(fma(-x, y, 1.0), y, y);
 }
 
+// The lanes of the mask as a per-lane condition: the select that uses it reads
+// the scalar mask, so a self test costs one scalar shift per pair instead of a
+// vector compare.
+__device__ __forceinline__ bool in_mask(uint64_t mask) {
+    return __builtin_amdgcn_inverse_ballot_w64(mask);
+}
+
 // One ordered pair (i = slot a of this thread, partner j at p), FP64.  The
-// self pair (r2 = 0) adds exactly zero.  IEEE: q = 1 / r2 by
-// the full division; otherwise recip_in_range (the same bits wherever the
-// cluster's energy is finite).
+// self pair (r2 = 0) adds exactly zero.  IEEE: q = 1 / r2 by the full
+// division; otherwise recip_in_range (the same bits wherever the cluster's
+// energy is finite).
 template <bool IEEE>
 __device__ __forceinline__ void pair_fp64(const double4 p, bool self, double xi, double yi,
                                           double zi, double k24, double km48, double& e,
@@ -377,10 +386,10 @@ __device__ __forceinline__ void pair_fp64(const double4 p, bool self, double xi,
     const double dy = yi - p.y;
     const double dz = zi - p.z;
     const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+    double q = IEEE ? 1.0 / r2 : recip_in_range(r2);
     // the self pair (r2 = 0) clears the high word of q: q is then zero or
     // subnormal, s6 = q^3 is exactly 0 and the pair adds exact zeros (one
     // select instead of two)
-    double q = IEEE ? 1.0 / r2 : recip_in_range(r2);
     int2 qb = *reinterpret_cast<int2*>(&q);
     qb.y = self ? 0 : qb.y;
     q = *reinterpret_cast<double*>(&qb);
@@ -466,48 +475,87 @@ __device__ __forceinline__ void pair_morse32(const float4 p, bool self, float xi
 // FP64: every operation rounded as written; partners are consumed in
 // ascending order, so each per-atom sum is reproducible.  Partner
 // coordinates are read from LDS in groups of kGroup64 ahead of the
-// arithmetic to cover the LDS latency.
+// arithmetic to cover the LDS latency.  Bound by FP64 issue (22 FP64
+// instructions per pair of Eq. (1), the reciprocal estimate counting four).
 constexpr int kGroup64 = 4;
 constexpr int kGroup32 = 8;
 
-// t: the atom index of this thread's slot 0 (atom a T + t is slot a).
-template <int A, int T, int POT, bool IEEE = true>
+// Partners j0 .. j1 - 1 (consecutive, ascending; j0 a multiple of kGroup64)
+// added to the sums of every slot.  SELF: the range lies in one 64-atom tile,
+// whose atom j is lane j mod 64 of slot `own`; otherwise no partner is an atom
+// of this wavefront.  PACKED: several clusters share the wavefront, so the
+// loop counter is not uniform and t (the lane's atom) is compared with it.
+template <int A, int POT, bool IEEE, bool SELF, bool PACKED>
+__device__ __forceinline__ void pairs_fp64_range(int j0, int j1, int own, int t,
+                                                 const double4* __restrict__ pos,
+                                                 const double (&x)[3][A], double (&e)[A],
+                                                 double (&g)[3][A], double rho, double c,
+                                                 double k24, double km48) {
+    auto pair = [&](const double4 p, bool self, int a) {
+        if constexpr (POT == kPairMorse)
+            pair_morse64(p, self, x[0][a], x[1][a], x[2][a], rho, c, e[a], g[0][a], g[1][a],
+                         g[2][a]);
+        else
+            pair_fp64<IEEE>(p, self, x[0][a], x[1][a], x[2][a], k24, km48, e[a], g[0][a], g[1][a],
+                            g[2][a]);
+    };
+    auto self_pair = [&](int j, uint64_t lanes, int a) {
+        if constexpr (!SELF) return false;
+        if constexpr (PACKED) return j == t;
+        return in_mask(A == 1 || own == a ? lanes : 0);
+    };
+    int j = j0;
+    for (; j + kGroup64 <= j1; j += kGroup64) {
+        double4 p[kGroup64];
+#pragma unroll
+        for (int u = 0; u < kGroup64; ++u) p[u] = pos[j + u];
+        uint64_t lanes = 1ull << (j & (kWave - 1));
+#pragma unroll
+        for (int u = 0; u < kGroup64; ++u, lanes <<= 1)
+#pragma unroll
+            for (int a = 0; a < A; ++a) pair(p[u], self_pair(j + u, lanes, a), a);
+    }
+    for (; j < j1; ++j) {
+        const double4 p = pos[j];
+        const uint64_t lanes = 1ull << (j & (kWave - 1));
+#pragma unroll
+        for (int a = 0; a < A; ++a) pair(p, self_pair(j, lanes, a), a);
+    }
+}
+
+// w: this wavefront's index in its team (slot a's own tile is a T / 64 + w);
+// t: the atom of this lane's slot 0.
+// Clusters that may span several tiles (W A > 1) run the loop tile by tile, so
+// that only the tiles which hold the wavefront's own atoms pay for the self
+// test.
+template <int A, int T, int POT, bool IEEE, bool PACKED = false>
 __device__ __forceinline__ void pairs_fp64(int n, const double4* __restrict__ pos,
                                            const double (&x)[3][A], double (&e)[A],
-                                           double (&g)[3][A], double rho, int t) {
+                                           double (&g)[3][A], double rho, int w, int t) {
     const double c = -2.0 * rho;
     // 24 and -48 held in registers for the whole loop: a 64-bit constant that
     // is not an inline one would otherwise be rebuilt by two moves per pair
     double k24 = 24.0, km48 = -48.0;
     asm volatile("" : "+v"(k24));
     asm volatile("" : "+s"(km48));
-    auto pair = [&](const double4 p, bool self, int a) {
-        if constexpr (POT == kPairMorse)
-            pair_morse64(p, self, x[0][a], x[1][a], x[2][a], rho, c, e[a], g[0][a], g[1][a],
-                         g[2][a]);
-        else
-            pair_fp64<IEEE>(p, self, x[0][a], x[1][a], x[2][a], k24, km48, e[a], g[0][a],
-                            g[1][a], g[2][a]);
-    };
 #pragma unroll
     for (int a = 0; a < A; ++a) {
         e[a] = 0.0;
         g[0][a] = g[1][a] = g[2][a] = 0.0;
     }
-    int j = 0;
-    for (; j + kGroup64 <= n; j += kGroup64) {
-        double4 p[kGroup64];
-#pragma unroll
-        for (int u = 0; u < kGroup64; ++u) p[u] = pos[j + u];
-#pragma unroll
-        for (int u = 0; u < kGroup64; ++u)
-#pragma unroll
-            for (int a = 0; a < A; ++a) pair(p[u], j + u == a * T + t, a);
-    }
-    for (; j < n; ++j) {
-        const double4 p = pos[j];
-#pragma unroll
-        for (int a = 0; a < A; ++a) pair(p, j == a * T + t, a);
+    if constexpr (A * T == kWave) {
+        pairs_fp64_range<A, POT, IEEE, true, PACKED>(0, n, 0, t, pos, x, e, g, rho, c, k24, km48);
+    } else {
+        constexpr int W = T / kWave;
+        for (int tile = 0; tile * kWave < n; ++tile) {
+            const int j0 = tile * kWave, j1 = min(n, j0 + kWave);
+            if (tile % W == w)
+                pairs_fp64_range<A, POT, IEEE, true, false>(j0, j1, tile / W, t, pos, x, e, g, rho,
+                                                            c, k24, km48);
+            else
+                pairs_fp64_range<A, POT, IEEE, false, false>(j0, j1, 0, t, pos, x, e, g, rho, c,
+                                                             k24, km48);
+        }
     }
 }
 

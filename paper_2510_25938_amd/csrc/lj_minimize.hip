@@ -253,7 +253,8 @@ struct Team {
                 return;
             }
         }
-        pairs_fp64<A, T, POT, IEEE>(n, pos64, x, e, g, rho, li);
+        pairs_fp64<A, T, POT, IEEE, (G > 1)>(
+            n, pos64, x, e, g, rho, W == 1 ? 0 : uniform((int)threadIdx.x / kWave), li);
     }
 
     __device__ __forceinline__ void sum_energy(double (&e)[1][A], double (&o)[1]) {
