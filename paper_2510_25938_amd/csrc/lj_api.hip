@@ -175,6 +175,16 @@ std::array<int, 4> class_key(int precision, int c, int max_n) {
 // Built-in rule for the shape of class c (0-2).
 int default_class_shape(int c, int max_n, int top_class, int mixed, int num, int cus) {
     const int cmax = class_cap(c, max_n);
+    // Helper wavefronts (FP64) while every cluster's workgroup is resident at
+    // once, so that they run on SIMDs which would idle: two workgroups per CU
+    // for class 0 by itself, one for class 1 or beside other classes.  8 x LJ38:
+    // 1.71 instead of 2.14 ms, 512 x LJ38 2.45 instead of 2.82 ms, 640 x LJ38
+    // 3.22 instead of 2.80 ms (hence the limit); 8 x LJ98 7.3 instead of
+    // 8.9 ms, 384 x LJ98 17.3 instead of 15.4 ms.  Below 20 atoms the hand-overs
+    // cost what the shared pairs save (LJ13 3.29 instead of 3.16 us per
+    // iteration, LJ20 3.86 instead of 3.97 us).
+    if (!mixed && c <= 1 && cmax >= 20 && num <= (c == 0 && top_class == 0 ? 2 : 1) * cus)
+        return lj::kRelayShape;
     if (c == 0) {
         // Several clusters per wavefront once the batch has more than two
         // clusters per SIMD: each wavefront then does the work of two or four
@@ -246,7 +256,8 @@ lj_status min_layout(int num, int max_n, int mixed, int pot, MinLayout& L,
     L.top_class = lj::class_of(max_n < 0 ? 0 : max_n);
     for (int c = 0; c <= L.top_class; ++c) {
         L.shape[c] = (force && force[c] >= 0) ? force[c] : class_schedule(prec, c, max_n, num, di.cus);
-        if (L.shape[c] < 0 || L.shape[c] >= lj::class_shapes(c) ||
+        if (L.shape[c] < 0 ||
+            (L.shape[c] >= lj::class_shapes(c) && L.shape[c] != lj::kRelayShape) ||
             lj::shape_max_n(c, L.shape[c]) < class_cap(c, max_n))
             return fail(LJ_E_ARG, "minimiser shape %d of class %d does not hold %d atoms",
                         L.shape[c], c, class_cap(c, max_n));
@@ -1082,8 +1093,13 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
                 }
             }
             if (s == LJ_OK) {
+                // the form with helper wavefronts has no number in the table:
+                // where it stays fastest, the built-in rule stays in charge
                 std::lock_guard<std::mutex> lk(g_sched_mu);
-                g_class_sched[class_key(precision, c, batch->max_n)] = chosen[c];
+                if (chosen[c] == lj::kRelayShape)
+                    g_class_sched.erase(class_key(precision, c, batch->max_n));
+                else
+                    g_class_sched[class_key(precision, c, batch->max_n)] = chosen[c];
             }
         }
         if (s == LJ_OK) best_min = cur;

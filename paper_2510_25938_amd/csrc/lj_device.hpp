@@ -183,6 +183,26 @@ __device__ __forceinline__ void wave_sum4(double a, double b, double c, double d
     out[3] = dpp<kDppNewBcast + 3>(v);
 }
 
+// wave_sum(a) + wave_sum(b), the sum over two atom slots per lane: after a first
+// level in which even lanes keep a and odd lanes keep b, one value per lane
+// goes through the other five levels (pairings that preserve the lane's
+// parity, as in wave_sum4), and a last exchange adds the two totals.  The same
+// additions as two wave_sum trees and their sum, for 31 instructions instead
+// of 45.
+__device__ __forceinline__ double wave_sum_slots(double a, double b) {
+    const bool odd = (__lane_id() & 1) != 0;
+    double v = (odd ? b : a) + dpp<kDppXor1>(odd ? a : b);
+    v = v + dpp<kDppXor2>(v);
+    v = v + dpp_xor4(v);
+    v = v + dpp<kDppRor8>(v);
+    double x, y;
+    swap_rows16(v, x, y);
+    v = x + y;
+    swap_halves32(v, x, y);
+    v = x + y;
+    return v + dpp<kDppXor1>(v);
+}
+
 template <int L = kWave>
 __device__ __forceinline__ double wave_max(double v) {
     static_assert(L == 16 || L == kWave, "16 or 64 leaves");
@@ -243,6 +263,10 @@ __device__ __forceinline__ void team_sum(double (&vals)[NV][A], double (&out)[NV
                                          TeamScratch<W, NVMAX>& sc, int& bank) {
     static_assert(NV * A <= NVMAX, "scratch too small");
     static_assert(L == kWave || (W == 1 && A == 1), "16 leaves: one wavefront, one slot");
+    if constexpr (W == 1 && A == 2 && NV == 1) {
+        out[0] = wave_sum_slots(vals[0][0], vals[0][1]);
+        return;
+    }
     double ws[NV][A];
 #pragma unroll
     for (int a = 0; a < A; ++a) {

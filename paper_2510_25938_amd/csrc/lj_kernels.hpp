@@ -91,6 +91,11 @@ constexpr int kUpMaxN = 40;
 int class_up_n(int c, int shape, int max_n, int pot);
 size_t class_dyn_lds(int c, int shape, int max_n, int pot);
 size_t class_hist_bytes_per_wg(int c, int shape);
+// The form with helper wavefronts (lj_relay.hip), a shape beside the numbered
+// ones that only the built-in rule chooses.
+constexpr int kRelayShape = 16;
+const void* relay_kernel_for(int mixed, int pot, int c);  // nullptr: none
+int relay_block();
 const void* minimize_kernel_for(int mixed, int pot, int c, int shape);
 hipError_t launch_plan(const int32_t* offset, int num, int max_n, const int32_t* active, Plan plan,
                        int32_t* status, hipStream_t st);
