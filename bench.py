@@ -33,7 +33,7 @@ FLOP_PER_PAIR = 27    # algorithmic FLOP per unique pair evaluation (E and gradi
 def kernel_source_hash():
     h = hashlib.sha256()
     for f in ("lj_device.hpp", "lj_kernels.hpp", "lj_lbfgs.hpp", "lj_minimize.hip",
-              "lj_relay.hip"):
+              "lj_relay.hip", "lj_split.hip"):
         with open(os.path.join(ROOT, "paper_2510_25938_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -131,6 +131,22 @@ typedef struct {
 lj_status lj_energy_grad_batch(const lj_batch* batch, const double* xyz, double* energy,
                                double* grad, int32_t precision, void* stream);
 
+/*
+ * lj_energy_grad_batch_ws - lj_energy_grad_batch with scratch memory, with
+ * which a call of a few large clusters spreads each of them over many
+ * workgroups.  Arguments, results (bit for bit) and errors are those of
+ * lj_energy_grad_batch.
+ *   ws, ws_bytes  workspace of lj_energy_grad_workspace_bytes() bytes, untouched
+ *                 until the enqueued work completes; with less (or NULL) the
+ *                 call runs as lj_energy_grad_batch.
+ * lj_energy_grad_workspace_bytes: 0 for batches that the call would not spread
+ * (and for invalid ones).
+ */
+size_t lj_energy_grad_workspace_bytes(const lj_batch* batch, int32_t precision);
+lj_status lj_energy_grad_batch_ws(const lj_batch* batch, const double* xyz, double* energy,
+                                  double* grad, int32_t precision, void* ws, size_t ws_bytes,
+                                  void* stream);
+
 /* L-BFGS parameters (host struct).  lj_lbfgs_defaults fills the defaults shown. */
 typedef struct {
     int32_t m;                  /* stored (s, y) pairs, 0..LJ_MAX_M             [10]   */

@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "liblj_bh.so")
-SOURCES = ["lj_minimize.hip", "lj_relay.hip", "lj_api.hip", "lj_bh_kernels.hip"]
+SOURCES = ["lj_minimize.hip", "lj_relay.hip", "lj_split.hip", "lj_api.hip", "lj_bh_kernels.hip"]
 HEADERS = ["lj_device.hpp", "lj_kernels.hpp", "lj_lbfgs.hpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -151,6 +151,37 @@ lj::EvalShape eval_schedule(int precision, int max_n) {
     return lj::eval_shape(max_n);
 }
 
+// Scratch bytes of the evaluation spread over many workgroups, 0 where one
+// workgroup per cluster is the faster (or the schedule table asks for a shape
+// other than the built-in one).  nt: 64-atom tiles of the largest cluster.
+//   FP64   one workgroup per tile, a round of the chip for every `cus` tiles,
+//          1.7 us per 64 partners and round, against 4.6, 6.4, 12 and 23 us
+//          per 64 partners at nt = 4, 8, 16 and 32 with one workgroup: 8 % more
+//          rounds than nt / 3 is level (64 x LJ500 41.7 instead of 56.5 us, 96
+//          59.3 instead of 58.1; 64 x LJ1000 134 instead of 191 us, 96 189
+//          instead of 200).  Up to 256 atoms the second launch costs what the
+//          split saves (8 x LJ256: 19.0 instead of 18.9 us).
+//   FP32   one wavefront per unit (a pair of tiles), 2.6 ns each and three
+//          launches (18 us), against 0.32 nt^2 us: 64 x LJ500 23.0 instead of
+//          27.8 us, 128 28.1 instead of 28.7; 128 x LJ1000 64.9 instead of
+//          90.3 us.  At most 40000 units (70 MB).
+size_t split_eval_ws(const lj_batch* b, int precision, int cus) {
+    const int mixed = precision == LJ_MIXED;
+    if (b->max_n <= 256) return 0;
+    const lj::EvalShape s = eval_schedule(precision, b->max_n), d = lj::eval_shape(b->max_n);
+    if (s.W != d.W || s.A != d.A) return 0;
+    const long nt = (b->max_n + 63) / 64;
+    if (!mixed) {
+        const long tiles = std::min((long)b->num * nt, (long)(b->total_atoms / 64) + b->num);
+        const long rounds = (tiles + cus - 1) / cus;
+        if (3 * rounds > nt + 1) return 0;
+    } else {
+        const long units = (long)b->num * lj::split_units(b->pair, (int)nt);
+        if (units > std::min(100 * nt * nt - 4000, 40000L)) return 0;
+    }
+    return lj::split_eval_bytes(mixed, b->pair, b->num, b->max_n);
+}
+
 int large_schedule(int precision) {
     std::lock_guard<std::mutex> lk(g_sched_mu);
     return g_large_sched[precision == LJ_MIXED ? 1 : 0];
@@ -656,8 +687,21 @@ void lj_lbfgs_defaults(lj_lbfgs_params* p) {
     p->ls_noise = 5e-7;
 }
 
+size_t lj_energy_grad_workspace_bytes(const lj_batch* batch, int32_t precision) {
+    if (check_batch(batch, LJ_MAX_ATOMS_EVAL, "lj_energy_grad_workspace_bytes") != LJ_OK) return 0;
+    DeviceInfo di;
+    if (batch->num == 0 || device_info(di) != LJ_OK) return 0;
+    return split_eval_ws(batch, precision, di.cus);
+}
+
 lj_status lj_energy_grad_batch(const lj_batch* batch, const double* xyz, double* energy,
                                double* grad, int32_t precision, void* stream) {
+    return lj_energy_grad_batch_ws(batch, xyz, energy, grad, precision, nullptr, 0, stream);
+}
+
+lj_status lj_energy_grad_batch_ws(const lj_batch* batch, const double* xyz, double* energy,
+                                  double* grad, int32_t precision, void* ws, size_t ws_bytes,
+                                  void* stream) {
     g_err.clear();
     lj_status s = check_batch(batch, LJ_MAX_ATOMS_EVAL, "lj_energy_grad_batch");
     if (s != LJ_OK) return s;
@@ -669,11 +713,19 @@ lj_status lj_energy_grad_batch(const lj_batch* batch, const double* xyz, double*
     DeviceInfo di;
     s = device_info(di);
     if (s != LJ_OK) return s;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const size_t need = ws ? split_eval_ws(batch, precision, di.cus) : 0;
+    if (need > 0 && ws_bytes >= need) {
+        LJ_HIP_TRY(lj::launch_split_eval(precision == LJ_MIXED, batch->pair, batch->num,
+                                         batch->max_n, batch->offset, batch->total_atoms, xyz,
+                                         energy, grad, batch->pair_rho, units_of(batch),
+                                         static_cast<char*>(ws), st));
+        return LJ_OK;
+    }
     LJ_HIP_TRY(lj::launch_energy_grad(precision == LJ_MIXED, batch->pair,
                                       eval_schedule(precision, batch->max_n), batch->num,
                                       batch->offset, batch->total_atoms, xyz, energy, grad,
-                                      batch->pair_rho, units_of(batch),
-                                      static_cast<hipStream_t>(stream)));
+                                      batch->pair_rho, units_of(batch), st));
     return LJ_OK;
 }
 
@@ -986,12 +1038,16 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
     const int cap = 2 * (pow2_at_least(need_slots) < 64 ? 64 : pow2_at_least(need_slots));
     lj::EvalShape best_shape = lj::eval_shape(batch->max_n);
     float best_ms = 1e30f;
+    const bool spread = split_eval_ws(batch, precision, di.cus) > 0;
     const int Ws[] = {1, 2, 4, 8, 16}, As[] = {1, 2, 4};
     for (int wi : Ws)
         for (int ai : As) {
             const int slots = 64 * wi * ai;
             if (slots < need_slots || slots > cap) continue;
             lj::EvalShape sh{wi, ai};
+            // a batch spread over many workgroups by the built-in rule keeps
+            // it (and its shape): an entry of another shape would end that
+            if (spread && (wi != best_shape.W || ai != best_shape.A)) continue;
             float ms = 0.f;
             s = time_it([&]() -> lj_status {
                 LJ_HIP_TRY(lj::launch_energy_grad(mixed, batch->pair, sh, batch->num,

@@ -496,6 +496,40 @@ __device__ __forceinline__ void pair_morse32(const float4 p, bool self, float xi
     gz = fmaf(f, dz, gz);
 }
 
+// 24 and -48 of the force factor held in registers for a whole loop: a 64-bit
+// constant that is not an inline one would otherwise be rebuilt by two moves
+// per pair.
+__device__ __forceinline__ void hold_constants(double& k24, double& km48) {
+    k24 = 24.0;
+    km48 = -48.0;
+    asm volatile("" : "+v"(k24));
+    asm volatile("" : "+s"(km48));
+}
+
+// One pair's terms: V's part et and the gradient coefficient f, with the
+// operations of pair_fp64 / pair_morse64 (the self pair: exact zeros).
+template <int POT, bool IEEE>
+__device__ __forceinline__ void pair_term64(double dx, double dy, double dz, bool self, double rho,
+                                            double c, double k24, double km48, double& f,
+                                            double& et) {
+    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+    if constexpr (POT == kPairMorse) {
+        const double r = sqrt(r2);
+        const double t = self ? 0.0 : exp_cw(fma(-rho, r, rho));
+        et = t * (t - 2.0);
+        const double fn = (c * t) * (t - 1.0);
+        f = self ? 0.0 : fn / r;
+    } else {
+        double q = IEEE ? 1.0 / r2 : recip_in_range(r2);
+        int2 qb = *reinterpret_cast<int2*>(&q);
+        qb.y = self ? 0 : qb.y;
+        q = *reinterpret_cast<double*>(&qb);
+        const double s6 = (q * q) * q;
+        et = fma(s6, s6, -s6);
+        f = (q * s6) * fma(km48, s6, k24);
+    }
+}
+
 // FP64: every operation rounded as written; partners are consumed in
 // ascending order, so each per-atom sum is reproducible.  Partner
 // coordinates are read from LDS in groups of kGroup64 ahead of the
@@ -557,11 +591,8 @@ __device__ __forceinline__ void pairs_fp64(int n, const double4* __restrict__ po
                                            const double (&x)[3][A], double (&e)[A],
                                            double (&g)[3][A], double rho, int w, int t) {
     const double c = -2.0 * rho;
-    // 24 and -48 held in registers for the whole loop: a 64-bit constant that
-    // is not an inline one would otherwise be rebuilt by two moves per pair
-    double k24 = 24.0, km48 = -48.0;
-    asm volatile("" : "+v"(k24));
-    asm volatile("" : "+s"(km48));
+    double k24, km48;
+    hold_constants(k24, km48);
 #pragma unroll
     for (int a = 0; a < A; ++a) {
         e[a] = 0.0;
@@ -830,6 +861,43 @@ __device__ __forceinline__ float3 tile_pair(const float4 pi, const float4* __res
     return make_float3(rx, ry, rz);
 }
 
+// Pairs of this lane's atom pi within its own tile (base: its doubled copy),
+// every pair of the tile once.  Returns the reaction on the lane's own atom.
+__device__ __forceinline__ float3 tile_diagonal(const float4 pi, const float4* __restrict__ base,
+                                                int lane, float& te, float& tx, float& ty,
+                                                float& tz) {
+    const float4* src = base + lane;
+    float rx = 0.0f, ry = 0.0f, rz = 0.0f;
+#pragma unroll 1
+    for (int k0 = 1; k0 <= kWave / 2; k0 += kGroup32) {  // ring distances 1 .. 32
+        float4 p[kGroup32];
+#pragma unroll
+        for (int u = 0; u < kGroup32; ++u) p[u] = src[k0 + u];
+#pragma unroll
+        for (int u = 0; u < kGroup32; ++u) {
+            const float dx = pi.x - p[u].x;
+            const float dy = pi.y - p[u].y;
+            const float dz = pi.z - p[u].z;
+            const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+            const float q = __builtin_amdgcn_rcpf(r2);
+            // distance 32 pairs lanes l and l + 32: lanes 0-31 take it
+            const bool dup = (u == kGroup32 - 1) && k0 + u == kWave / 2 && lane >= kWave / 2;
+            const float s6 = dup ? 0.0f : (q * q) * q;
+            te = te + fmaf(s6, s6, -s6);
+            const float f = (q * s6) * fmaf(-48.0f, s6, 24.0f);
+            tx = fmaf(f, dx, tx);
+            ty = fmaf(f, dy, ty);
+            tz = fmaf(f, dz, tz);
+            rx = rol1(rx) - f * dx;
+            ry = rol1(ry) - f * dy;
+            rz = rol1(rz) - f * dz;
+        }
+    }
+    // lane l now holds the reaction on atom l + 32: swap the two halves
+    return make_float3(swap_half_lanes(rx, lane), swap_half_lanes(ry, lane),
+                       swap_half_lanes(rz, lane));
+}
+
 // ---------------------------------------------------------------------------
 // FP32 pair terms (Eq. (1) or the Morse pair) over unique pairs for
 // one-wavefront clusters of kRingMin <= n <= 43 atoms: a ring of period n.
@@ -955,38 +1023,8 @@ __device__ __forceinline__ void pairs_tiles(int n, const float4* __restrict__ po
         g[0][a] = g[1][a] = g[2][a] = 0.0;
         const int tau = a * W + w;
         if (tau >= nt) continue;
-        const float4 pi = pos[128 * tau + lane];
-        const float4* src = pos + 128 * tau + lane;
         float te = 0.0f, tx = 0.0f, ty = 0.0f, tz = 0.0f;
-        float rx = 0.0f, ry = 0.0f, rz = 0.0f;
-#pragma unroll 1
-        for (int k0 = 1; k0 <= kWave / 2; k0 += kGroup32) {  // ring distances 1 .. 32
-            float4 p[kGroup32];
-#pragma unroll
-            for (int u = 0; u < kGroup32; ++u) p[u] = src[k0 + u];
-#pragma unroll
-            for (int u = 0; u < kGroup32; ++u) {
-                const float dx = pi.x - p[u].x;
-                const float dy = pi.y - p[u].y;
-                const float dz = pi.z - p[u].z;
-                const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                const float q = __builtin_amdgcn_rcpf(r2);
-                // distance 32 pairs lanes l and l + 32: lanes 0-31 take it
-                const bool dup = (u == kGroup32 - 1) && k0 + u == kWave / 2 && lane >= kWave / 2;
-                const float s6 = dup ? 0.0f : (q * q) * q;
-                te = te + fmaf(s6, s6, -s6);
-                const float f = (q * s6) * fmaf(-48.0f, s6, 24.0f);
-                tx = fmaf(f, dx, tx);
-                ty = fmaf(f, dy, ty);
-                tz = fmaf(f, dz, tz);
-                rx = rol1(rx) - f * dx;
-                ry = rol1(ry) - f * dy;
-                rz = rol1(rz) - f * dz;
-            }
-        }
-        // lane l now holds the reaction on atom l + 32: swap the two halves
-        const float3 r = make_float3(swap_half_lanes(rx, lane), swap_half_lanes(ry, lane),
-                                     swap_half_lanes(rz, lane));
+        const float3 r = tile_diagonal(pos[128 * tau + lane], pos + 128 * tau, lane, te, tx, ty, tz);
         e[a] += 2.0 * (double)te;
         g[0][a] += (double)tx;
         g[1][a] += (double)ty;

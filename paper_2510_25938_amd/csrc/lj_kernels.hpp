@@ -75,6 +75,14 @@ bool eval_shape_supported(EvalShape s);
 hipError_t launch_energy_grad(int mixed, int pot, EvalShape s, int num, const int32_t* off,
                               int64_t total, const double* xyz, double* e, double* g, double rho,
                               Units u, hipStream_t st);
+// The evaluation of a few large clusters over many workgroups (lj_split.hip),
+// with the results of launch_energy_grad in its built-in shape, and the
+// scratch memory it takes.
+int split_units(int pot, int nt);  // FP32 tile pairs of a cluster of nt tiles
+size_t split_eval_bytes(int mixed, int pot, int num, int max_n);
+hipError_t launch_split_eval(int mixed, int pot, int num, int max_n, const int32_t* off,
+                             int64_t total, const double* xyz, double* energy, double* grad,
+                             double rho, Units u, char* ws, hipStream_t st);
 // Minimiser shapes per size class (see lj_minimize.hip): class_shapes(c)
 // interchangeable kernels; shape s holds clusters of at most
 // shape_max_n(c, s) atoms, shape_clusters_per_wg(c, s) of them per workgroup.

@@ -34,30 +34,6 @@ struct RelayLds {
     int cmd, n;
 };
 
-// One pair's terms: V's part et and the gradient coefficient f, with the
-// operations of pair_fp64 / pair_morse64 (the self pair: exact zeros).
-template <int POT, bool IEEE>
-__device__ __forceinline__ void pair_term64(double dx, double dy, double dz, bool self, double rho,
-                                            double c, double k24, double km48, double& f,
-                                            double& et) {
-    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-    if constexpr (POT == kPairMorse) {
-        const double r = sqrt(r2);
-        const double t = self ? 0.0 : exp_cw(fma(-rho, r, rho));
-        et = t * (t - 2.0);
-        const double fn = (c * t) * (t - 1.0);
-        f = self ? 0.0 : fn / r;
-    } else {
-        double q = IEEE ? 1.0 / r2 : recip_in_range(r2);
-        int2 qb = *reinterpret_cast<int2*>(&q);
-        qb.y = self ? 0 : qb.y;
-        q = *reinterpret_cast<double*>(&qb);
-        const double s6 = (q * q) * q;
-        et = fma(s6, s6, -s6);
-        f = (q * s6) * fma(km48, s6, k24);
-    }
-}
-
 // First partner of segment s of S (s = S: n).  Segments grow, so that a
 // wavefront's terms are ready when its predecessor hands over: with t
 // instructions per term (21 for Eq. (1), about 70 for the Morse pair), 4 per
@@ -107,13 +83,6 @@ __device__ __forceinline__ void relay_first(RelayLds<A>& lds, int j1, int tile, 
                                                      km48);
     lds.acc[tile][0][lane] = make_double2(e[0], g[0][0]);
     lds.acc[tile][1][lane] = make_double2(g[1][0], g[2][0]);
-}
-
-__device__ __forceinline__ void hold_constants(double& k24, double& km48) {
-    k24 = 24.0;
-    km48 = -48.0;
-    asm volatile("" : "+v"(k24));
-    asm volatile("" : "+s"(km48));
 }
 
 // Helper of a one-tile cluster (segment seg >= 1): NG groups of 4 terms and

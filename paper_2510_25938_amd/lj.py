@@ -18,6 +18,7 @@ FP64, MIXED = 0, 1
 CONVERGED, MAXITER, LSFAIL, NONFINITE, SWITCHED, BADSIZE = 0, 1, 2, 3, 4, 5
 OK, E_ARG, E_HIP, E_WORKSPACE, E_UNSUPPORTED = 0, -1, -2, -3, -4
 MAX_ATOMS_EVAL, MAX_ATOMS_MIN, MAX_M, MAX_CANDS = 4096, 1024, 10, 64
+SPLIT_EVAL_MIN_ATOMS = 257  # smaller clusters are never spread over workgroups
 SCHED_EVAL, SCHED_MIN_LARGE = 0, 1
 SCHED_MIN_CLASS = (2, 3, 4)  # minimiser shape of size classes 0, 1, 2
 # shapes per class: (clusters per workgroup, largest N) for each shape index
@@ -27,7 +28,7 @@ EXPORTED = ["lj_energy_grad_batch", "lj_lbfgs_defaults", "lj_minimize_workspace_
             "lj_bh_minimize_batch", "lj_bh_workspace_bytes", "lj_bh_step", "lj_set_schedule",
             "lj_get_schedule", "lj_autotune_workspace_bytes", "lj_autotune", "lj_status_string",
             "lj_last_error", "lj_abi_version", "lj_bh_minimize_batch_noalloc",
-            "lj_bh_graph_captures"]
+            "lj_bh_graph_captures", "lj_energy_grad_workspace_bytes", "lj_energy_grad_batch_ws"]
 NOALLOC_SCRATCH_BYTES, NOALLOC_MAX_ATOMS, NOALLOC_MAX_CLUSTERS = 1 << 20, 256, 262016
 
 
@@ -80,6 +81,10 @@ def lib():
         vp, i32 = C.c_void_p, C.c_int32
         L.lj_energy_grad_batch.argtypes = [C.POINTER(Batch), vp, vp, vp, i32, vp]
         L.lj_energy_grad_batch.restype = i32
+        L.lj_energy_grad_workspace_bytes.argtypes = [C.POINTER(Batch), i32]
+        L.lj_energy_grad_workspace_bytes.restype = C.c_size_t
+        L.lj_energy_grad_batch_ws.argtypes = [C.POINTER(Batch), vp, vp, vp, i32, vp, C.c_size_t, vp]
+        L.lj_energy_grad_batch_ws.restype = i32
         L.lj_lbfgs_defaults.argtypes = [C.POINTER(LbfgsParams)]
         L.lj_lbfgs_defaults.restype = None
         L.lj_minimize_workspace_bytes.argtypes = [C.POINTER(Batch), C.POINTER(LbfgsParams), i32]
@@ -200,10 +205,18 @@ def energy_grad(batch, xyz, precision="fp64", grad=True, stream=None, sigma=1.0,
     assert xyz.dtype == torch.float64 and xyz.is_contiguous() and xyz.shape == (3, batch.total)
     E = torch.empty(batch.num, dtype=torch.float64, device=xyz.device)
     g = torch.empty_like(xyz) if grad else None
+    desc = C.byref(batch.desc(sigma=sigma, epsilon=epsilon))
+    prec = precision_code(precision)
+    if batch.max_n >= SPLIT_EVAL_MIN_ATOMS:  # a few large clusters take scratch memory
+        nb = int(lib().lj_energy_grad_workspace_bytes(desc, prec))
+        if nb:
+            ws = torch.empty(nb, dtype=torch.uint8, device=xyz.device)
+            _order(stream, xyz, E, g, batch.offset, ws)
+            _check(lib().lj_energy_grad_batch_ws(desc, _ptr(xyz), _ptr(E), _ptr(g), prec, _ptr(ws),
+                                                 nb, _stream(stream)))
+            return E, g
     _order(stream, xyz, E, g, batch.offset)
-    _check(lib().lj_energy_grad_batch(C.byref(batch.desc(sigma=sigma, epsilon=epsilon)),
-                                      _ptr(xyz), _ptr(E), _ptr(g), precision_code(precision),
-                                      _stream(stream)))
+    _check(lib().lj_energy_grad_batch(desc, _ptr(xyz), _ptr(E), _ptr(g), prec, _stream(stream)))
     return E, g
 
 
