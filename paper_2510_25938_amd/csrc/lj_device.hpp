@@ -245,6 +245,30 @@ __device__ __forceinline__ double tree_w(const double* r) {
     }
 }
 
+// The same sum (and the maximum) of W = 8 or 16 values in LDS, one per lane of
+// every group of W lanes and added by the row levels of wave_sum: one LDS read
+// per lane instead of W.  Every lane ends with the result.
+template <int W>
+__device__ __forceinline__ double lane_tree(const double* r) {
+    static_assert(W == 8 || W == 16, "row levels");
+    double v = r[threadIdx.x % W];
+    v = v + dpp<kDppXor1>(v);
+    v = v + dpp<kDppXor2>(v);
+    v = v + dpp<kDppHalfMirror>(v);
+    if constexpr (W == 16) v = v + dpp<kDppMirror>(v);
+    return v;
+}
+template <int W>
+__device__ __forceinline__ double lane_max(const double* r) {
+    static_assert(W == 8 || W == 16, "row levels");
+    double v = r[threadIdx.x % W];
+    v = fmax(v, dpp<kDppXor1>(v));
+    v = fmax(v, dpp<kDppXor2>(v));
+    v = fmax(v, dpp<kDppHalfMirror>(v));
+    if constexpr (W == 16) v = fmax(v, dpp<kDppMirror>(v));
+    return v;
+}
+
 // Team reduction scratch in LDS: two alternating banks of NV x W doubles.
 // One barrier per reduction: a bank is rewritten only two reductions later,
 // and every thread has passed the intermediate reduction's barrier (after
@@ -303,10 +327,14 @@ __device__ __forceinline__ void team_sum(double (&vals)[NV][A], double (&out)[NV
             double r[A];
 #pragma unroll
             for (int a = 0; a < A; ++a) {
-                double rw[W];
+                if constexpr (W >= 8) {
+                    r[a] = lane_tree<W>(sc.v[bank][k * A + a]);
+                } else {
+                    double rw[W];
 #pragma unroll
-                for (int q = 0; q < W; ++q) rw[q] = sc.v[bank][k * A + a][q];
-                r[a] = tree_w<W>(rw);
+                    for (int q = 0; q < W; ++q) rw[q] = sc.v[bank][k * A + a][q];
+                    r[a] = tree_w<W>(rw);
+                }
             }
             out[k] = uniform(tree<A>(r));  // identical in every lane
         }
@@ -328,8 +356,12 @@ __device__ __forceinline__ double team_max(const double (&vals)[A], TeamScratch<
         if (threadIdx.x % kWave == 0) sc.v[bank][0][w] = m;
         __syncthreads();
         double r = sc.v[bank][0][0];
+        if constexpr (W >= 8) {
+            r = lane_max<W>(sc.v[bank][0]);
+        } else {
 #pragma unroll
-        for (int q = 1; q < W; ++q) r = fmax(r, sc.v[bank][0][q]);
+            for (int q = 1; q < W; ++q) r = fmax(r, sc.v[bank][0][q]);
+        }
         bank ^= 1;
         return uniform(r);
     }
@@ -543,7 +575,8 @@ constexpr int kGroup32 = 8;
 // whose atom j is lane j mod 64 of slot `own`; otherwise no partner is an atom
 // of this wavefront.  PACKED: several clusters share the wavefront, so the
 // loop counter is not uniform and t (the lane's atom) is compared with it.
-template <int A, int POT, bool IEEE, bool SELF, bool PACKED>
+// NA: the slots that hold atoms (the others' sums stay as they are).
+template <int A, int POT, bool IEEE, bool SELF, bool PACKED, int NA = A>
 __device__ __forceinline__ void pairs_fp64_range(int j0, int j1, int own, int t,
                                                  const double4* __restrict__ pos,
                                                  const double (&x)[3][A], double (&e)[A],
@@ -571,14 +604,26 @@ __device__ __forceinline__ void pairs_fp64_range(int j0, int j1, int own, int t,
 #pragma unroll
         for (int u = 0; u < kGroup64; ++u, lanes <<= 1)
 #pragma unroll
-            for (int a = 0; a < A; ++a) pair(p[u], self_pair(j + u, lanes, a), a);
+            for (int a = 0; a < NA; ++a) pair(p[u], self_pair(j + u, lanes, a), a);
     }
     for (; j < j1; ++j) {
         const double4 p = pos[j];
         const uint64_t lanes = 1ull << (j & (kWave - 1));
 #pragma unroll
-        for (int a = 0; a < A; ++a) pair(p, self_pair(j, lanes, a), a);
+        for (int a = 0; a < NA; ++a) pair(p, self_pair(j, lanes, a), a);
     }
+}
+
+template <int N>
+struct SlotCount {
+    static constexpr int value = N;
+};
+
+// The slots of wavefront w that hold atoms of a cluster of n.
+template <int A, int T>
+__device__ __forceinline__ int used_slots(int n, int w) {
+    const int rest = n - w * kWave;
+    return rest <= 0 ? 0 : min(A, (rest + T - 1) / T);
 }
 
 // w: this wavefront's index in its team (slot a's own tile is a T / 64 + w);
@@ -601,15 +646,32 @@ __device__ __forceinline__ void pairs_fp64(int n, const double4* __restrict__ po
     if constexpr (A * T == kWave) {
         pairs_fp64_range<A, POT, IEEE, true, PACKED>(0, n, 0, t, pos, x, e, g, rho, c, k24, km48);
     } else {
+        // slots above the cluster's last atom do no work (a 300-atom cluster in
+        // an 8 x 2 team: 5 of 8 wavefronts, one slot each)
         constexpr int W = T / kWave;
-        for (int tile = 0; tile * kWave < n; ++tile) {
-            const int j0 = tile * kWave, j1 = min(n, j0 + kWave);
-            if (tile % W == w)
-                pairs_fp64_range<A, POT, IEEE, true, false>(j0, j1, tile / W, t, pos, x, e, g, rho,
-                                                            c, k24, km48);
+        auto run = [&](auto na) {
+            constexpr int NA = decltype(na)::value;
+            for (int tile = 0; tile * kWave < n; ++tile) {
+                const int j0 = tile * kWave, j1 = min(n, j0 + kWave);
+                if (tile % W == w)
+                    pairs_fp64_range<A, POT, IEEE, true, false, NA>(j0, j1, tile / W, t, pos, x, e,
+                                                                    g, rho, c, k24, km48);
+                else
+                    pairs_fp64_range<A, POT, IEEE, false, false, NA>(j0, j1, 0, t, pos, x, e, g,
+                                                                     rho, c, k24, km48);
+            }
+        };
+        const int slots = used_slots<A, T>(n, w);
+        if (slots == 0) return;
+        if constexpr (A == 1 || W == 1) {
+            run(SlotCount<A>{});
+        } else {
+            if (slots == 1)
+                run(SlotCount<1>{});
+            else if (A == 2 || slots == 2)
+                run(SlotCount<2>{});
             else
-                pairs_fp64_range<A, POT, IEEE, false, false>(j0, j1, 0, t, pos, x, e, g, rho, c,
-                                                             k24, km48);
+                run(SlotCount<A>{});
         }
     }
 }
@@ -718,25 +780,23 @@ __device__ __forceinline__ void pairs_morse64_up(int n, const double4* __restric
 
 // FP32 pair arithmetic and FP32 accumulation over tiles of kTileJ partners;
 // each tile's per-atom partial sums are added into FP64 accumulators.
-template <int A, int T, int POT>
-__device__ __forceinline__ void pairs_mixed(int n, const float4* __restrict__ pos,
-                                            const double (&x)[3][A], double (&e)[A],
-                                            double (&g)[3][A], double rho, int t) {
+template <int A, int T, int POT, int NA>
+__device__ __forceinline__ void pairs_mixed_slots(int n, const float4* __restrict__ pos,
+                                                  const double (&x)[3][A], double (&e)[A],
+                                                  double (&g)[3][A], double rho, int t) {
     const float rf = (float)rho, cf = -2.0f * rf;
-    float xf[3][A];
+    float xf[3][NA];
 #pragma unroll
-    for (int a = 0; a < A; ++a) {
-        e[a] = 0.0;
-        g[0][a] = g[1][a] = g[2][a] = 0.0;
+    for (int a = 0; a < NA; ++a) {
         xf[0][a] = (float)x[0][a];
         xf[1][a] = (float)x[1][a];
         xf[2][a] = (float)x[2][a];
     }
     for (int j0 = 0; j0 < n; j0 += kTileJ) {
         const int j1 = min(n, j0 + kTileJ);
-        float te[A], tg[3][A];
+        float te[NA], tg[3][NA];
 #pragma unroll
-        for (int a = 0; a < A; ++a) te[a] = tg[0][a] = tg[1][a] = tg[2][a] = 0.0f;
+        for (int a = 0; a < NA; ++a) te[a] = tg[0][a] = tg[1][a] = tg[2][a] = 0.0f;
         auto pair = [&](const float4 p, bool self, int a) {
             if constexpr (POT == kPairMorse)
                 pair_morse32(p, self, xf[0][a], xf[1][a], xf[2][a], rf, cf, te[a], tg[0][a],
@@ -753,20 +813,45 @@ __device__ __forceinline__ void pairs_mixed(int n, const float4* __restrict__ po
 #pragma unroll
             for (int u = 0; u < kGroup32; ++u)
 #pragma unroll
-                for (int a = 0; a < A; ++a) pair(p[u], j + u == a * T + t, a);
+                for (int a = 0; a < NA; ++a) pair(p[u], j + u == a * T + t, a);
         }
         for (; j < j1; ++j) {
             const float4 p = pos[j];
 #pragma unroll
-            for (int a = 0; a < A; ++a) pair(p, j == a * T + t, a);
+            for (int a = 0; a < NA; ++a) pair(p, j == a * T + t, a);
         }
 #pragma unroll
-        for (int a = 0; a < A; ++a) {
+        for (int a = 0; a < NA; ++a) {
             e[a] += (double)te[a];
             g[0][a] += (double)tg[0][a];
             g[1][a] += (double)tg[1][a];
             g[2][a] += (double)tg[2][a];
         }
+    }
+}
+
+// As pairs_fp64, slots above the cluster's last atom do no work (w: this
+// wavefront's index in its team).
+template <int A, int T, int POT>
+__device__ __forceinline__ void pairs_mixed(int n, const float4* __restrict__ pos,
+                                            const double (&x)[3][A], double (&e)[A],
+                                            double (&g)[3][A], double rho, int w, int t) {
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+        e[a] = 0.0;
+        g[0][a] = g[1][a] = g[2][a] = 0.0;
+    }
+    if constexpr (T == kWave) {
+        pairs_mixed_slots<A, T, POT, A>(n, pos, x, e, g, rho, t);
+    } else {
+        const int slots = used_slots<A, T>(n, w);
+        if (slots == 0) return;
+        if (A == 1 || slots == 1)
+            pairs_mixed_slots<A, T, POT, 1>(n, pos, x, e, g, rho, t);
+        else if (A == 2 || slots == 2)
+            pairs_mixed_slots<A, T, POT, A < 2 ? A : 2>(n, pos, x, e, g, rho, t);
+        else
+            pairs_mixed_slots<A, T, POT, A>(n, pos, x, e, g, rho, t);
     }
 }
 

@@ -153,14 +153,22 @@ struct Team {
             double r[A];
 #pragma unroll
             for (int a = 0; a < A; ++a) {
-                double rw[W];
+                if constexpr (W >= 8) {
+                    r[a] = lane_tree<W>(sc->v[bank][a]);
+                } else {
+                    double rw[W];
 #pragma unroll
-                for (int q = 0; q < W; ++q) rw[q] = sc->v[bank][a][q];
-                r[a] = tree_w<W>(rw);
+                    for (int q = 0; q < W; ++q) rw[q] = sc->v[bank][a][q];
+                    r[a] = tree_w<W>(rw);
+                }
             }
             double mx = sc->v[bank][A][0];
+            if constexpr (W >= 8) {
+                mx = lane_max<W>(sc->v[bank][A]);
+            } else {
 #pragma unroll
-            for (int q = 1; q < W; ++q) mx = fmax(mx, sc->v[bank][A][q]);
+                for (int q = 1; q < W; ++q) mx = fmax(mx, sc->v[bank][A][q]);
+            }
             bank ^= 1;
             uv = uniform(tree<A>(r));
             vmax2 = uniform(mx);
@@ -215,7 +223,8 @@ struct Team {
         } else if (tiles) {
             if constexpr (kTiles) pairs_tiles<W, A>(n, pos32, rbuf, e[0], g);
         } else if constexpr (F32) {
-            pairs_mixed<A, T, POT>(n, pos32, x, e[0], g, rho, li);
+            pairs_mixed<A, T, POT>(n, pos32, x, e[0], g, rho,
+                                   W == 1 ? 0 : uniform((int)threadIdx.x / kWave), li);
         } else {
             fp64_pairs<POT == kPairMorse>(x, e[0], g);
         }
@@ -275,7 +284,7 @@ struct History<W, A, true> {
     int hist = 0;
     double gamma = 1.0;
 
-    __device__ __forceinline__ void init(double*, int) { hist = 0; gamma = 1.0; }
+    __device__ __forceinline__ void init(double*, double*, int) { hist = 0; gamma = 1.0; }
     __device__ __forceinline__ void clear() { hist = 0; }
 
     __device__ __forceinline__ void push(const double (&s)[3][A], const double (&y)[3][A], double r,
@@ -372,21 +381,54 @@ struct History<W, A, true> {
     }
 };
 
+// In global memory: a ring of kMaxM slots per workgroup; a slot holds, per atom
+// slot and thread, the pair (s, y) as three 16-byte words, so a wavefront reads
+// 1 KB at a time.  At N = 1000 the 256 rings (123 MB) are read from the last-level
+// cache twice per iteration.  Both recursions read ahead of the reductions
+// (their barriers wait for LDS only, so reads stay in flight across them), and
+// the oldest kKeep pairs, the last of the first recursion and the first of the
+// second, are kept in registers in between.  rho and the alphas, uniform over
+// the workgroup, live in LDS (written by thread 0, read after a reduction's
+// barrier) instead of 40 registers.  256 x LJ1000, per iteration: FP32 phase
+// 127 -> 99 us, FP64 253 -> 220 us; 256 x LJ300 FP32 phase 63 -> 33 us (with 3 or
+// 4 pairs kept at A = 1: 102 and 103 us, spills).
 template <int W, int A>
 struct History<W, A, false> {
     static constexpr int T = kWave * W;
-    double* base;  // this workgroup's ring: S slots then Y slots, [slot][3][A][T]
-    double rho[kMaxM];
+    static constexpr int kSlot = 3 * A * T;  // double2 per slot
+    static constexpr int kKeep = A == 1 ? 2 : A == 2 ? 3 : 1;
+    double2* base;
+    double* rho;    // LDS [slot]
+    double* alpha;  // LDS [age]
     int hist = 0;
     int newest = -1;
     int m = 1;
     double gamma = 1.0;
 
-    __device__ __forceinline__ double* vec(int slot, bool isY) const {
-        return base + ((size_t)((isY ? kMaxM : 0) + slot) * 3 * A) * T + threadIdx.x;
-    }
-    __device__ __forceinline__ void init(double* b, int mm) {
-        base = b;
+    struct Pair {
+        double2 v[A][3];  // (sx, sy), (sz, yx), (yy, yz)
+        __device__ __forceinline__ void s(double (&o)[3][A]) const {
+#pragma unroll
+            for (int q = 0; q < A; ++q) {
+                o[0][q] = v[q][0].x;
+                o[1][q] = v[q][0].y;
+                o[2][q] = v[q][1].x;
+            }
+        }
+        __device__ __forceinline__ void y(double (&o)[3][A]) const {
+#pragma unroll
+            for (int q = 0; q < A; ++q) {
+                o[0][q] = v[q][1].y;
+                o[1][q] = v[q][2].x;
+                o[2][q] = v[q][2].y;
+            }
+        }
+    };
+
+    __device__ __forceinline__ void init(double* b, double* lds, int mm) {
+        base = reinterpret_cast<double2*>(b) + threadIdx.x;
+        rho = lds;
+        alpha = lds + kMaxM;
         m = mm > 0 ? mm : 1;
         hist = 0;
         newest = -1;
@@ -394,71 +436,105 @@ struct History<W, A, false> {
     }
     __device__ __forceinline__ void clear() { hist = 0; }
 
+    __device__ __forceinline__ int slot(int age) const {
+        const int k = newest - age;
+        return k < 0 ? k + m : k;
+    }
+    __device__ __forceinline__ Pair load(int age) const {
+        const double2* p = base + (size_t)slot(age) * kSlot;
+        Pair r;
+#pragma unroll
+        for (int q = 0; q < A; ++q)
+#pragma unroll
+            for (int w = 0; w < 3; ++w) r.v[q][w] = p[(q * 3 + w) * T];
+        return r;
+    }
+
     __device__ __forceinline__ void push(const double (&s)[3][A], const double (&y)[3][A], double r,
                                          double gam, int mm) {
-        newest = (newest + 1) % m;
-        double* ps = vec(newest, false);
-        double* py = vec(newest, true);
+        newest = newest + 1 == m ? 0 : newest + 1;
+        double2* p = base + (size_t)newest * kSlot;
+#pragma unroll
+        for (int q = 0; q < A; ++q) {
+            p[(q * 3 + 0) * T] = make_double2(s[0][q], s[1][q]);
+            p[(q * 3 + 1) * T] = make_double2(s[2][q], y[0][q]);
+            p[(q * 3 + 2) * T] = make_double2(y[1][q], y[2][q]);
+        }
+        if (threadIdx.x == 0) rho[newest] = r;
+        gamma = gam;
+        hist = hist < mm ? hist + 1 : mm;
+    }
+
+    // r <- r - a y, a = rho s.r
+    template <class TM>
+    __device__ __forceinline__ void first(TM& tm, const Pair& p, int age, double (&r)[3][A]) {
+        double v[3][A];
+        p.s(v);
+        const double sr = tm.dot(v, r);
+        const double a = rho[slot(age)] * sr;
+        if (threadIdx.x == 0) alpha[age] = a;
+        p.y(v);
 #pragma unroll
         for (int c = 0; c < 3; ++c)
 #pragma unroll
-            for (int a = 0; a < A; ++a) {
-                ps[(c * A + a) * T] = s[c][a];
-                py[(c * A + a) * T] = y[c][a];
-            }
+            for (int q = 0; q < A; ++q) r[c][q] = fma(-a, v[c][q], r[c][q]);
+    }
+    // r <- r + (alpha - rho y.r) s
+    template <class TM>
+    __device__ __forceinline__ void second(TM& tm, const Pair& p, int age, double (&r)[3][A]) {
+        double v[3][A];
+        p.y(v);
+        const double yr = tm.dot(v, r);
+        const double b = rho[slot(age)] * yr;
+        const double w = alpha[age] - b;
+        p.s(v);
 #pragma unroll
-        for (int k = kMaxM - 1; k > 0; --k) rho[k] = rho[k - 1];
-        rho[0] = r;
-        gamma = gam;
-        hist = hist < mm ? hist + 1 : mm;
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int q = 0; q < A; ++q) r[c][q] = fma(w, v[c][q], r[c][q]);
     }
 
     template <class TM>
     __device__ __forceinline__ void apply(TM& tm, double (&r)[3][A]) {
         const int h = tm.uni(hist);
-        double al[kMaxM];
-        double v[3][A];
-#pragma unroll
-        for (int k = 0; k < kMaxM; ++k) {
-            if (k < h) {
-                const int slot = (newest - k + m) % m;
-                const double* ps = vec(slot, false);
-                const double* py = vec(slot, true);
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-#pragma unroll
-                    for (int q = 0; q < A; ++q) v[c][q] = ps[(c * A + q) * T];
-                const double a = rho[k] * tm.dot(v, r);
-                al[k] = a;
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-#pragma unroll
-                    for (int q = 0; q < A; ++q) r[c][q] = fma(-a, py[(c * A + q) * T], r[c][q]);
+        if (h == 0) return;
+        const int keep = h < kKeep ? h : kKeep;
+        const int cut = h - keep;  // ages cut .. h - 1 are kept between the recursions
+        Pair kept[kKeep];
+        if (cut > 0) {
+            Pair cur = load(0), next = load(1);
+#pragma unroll 1
+            for (int k = 0; k < cut; ++k) {
+                const Pair ahead = load(k + 2 < h ? k + 2 : h - 1);
+                first(tm, cur, k, r);
+                cur = next;
+                next = ahead;
             }
-        }
-        if (h > 0) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int q = 0; q < A; ++q) r[c][q] = gamma * r[c][q];
+            kept[0] = cur;
+            if constexpr (kKeep > 1) kept[1] = next;
+        } else {
+            kept[0] = load(0);
+            if constexpr (kKeep > 1) kept[1] = load(h > 1 ? 1 : 0);
         }
 #pragma unroll
-        for (int k = kMaxM - 1; k >= 0; --k) {
-            if (k < h) {
-                const int slot = (newest - k + m) % m;
-                const double* ps = vec(slot, false);
-                const double* py = vec(slot, true);
+        for (int c = 2; c < kKeep; ++c) kept[c] = load(cut + c < h ? cut + c : h - 1);
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
+        for (int c = 0; c < kKeep; ++c)
+            if (c < keep) first(tm, kept[c], cut + c, r);
 #pragma unroll
-                    for (int q = 0; q < A; ++q) v[c][q] = py[(c * A + q) * T];
-                const double b = rho[k] * tm.dot(v, r);
-                const double w = al[k] - b;
+        for (int c = 0; c < 3; ++c)
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
+            for (int q = 0; q < A; ++q) r[c][q] = gamma * r[c][q];
+        Pair cur = load(cut > 0 ? cut - 1 : 0), next = load(cut > 1 ? cut - 2 : 0);
 #pragma unroll
-                    for (int q = 0; q < A; ++q) r[c][q] = fma(w, ps[(c * A + q) * T], r[c][q]);
-            }
+        for (int c = kKeep - 1; c >= 0; --c)
+            if (c < keep) second(tm, kept[c], cut + c, r);
+#pragma unroll 1
+        for (int k = cut - 1; k >= 0; --k) {
+            const Pair ahead = load(k > 2 ? k - 2 : 0);
+            second(tm, cur, k, r);
+            cur = next;
+            next = ahead;
         }
     }
 };

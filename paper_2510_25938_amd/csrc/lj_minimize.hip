@@ -57,7 +57,8 @@ __global__ __launch_bounds__(kWave* W) __attribute__((amdgpu_waves_per_eu(OCC)))
     tm.rho = args.rho;
     History<W, A, HREG> H;
     constexpr size_t kHistPerWG = (size_t)2 * kMaxM * 3 * A * T;
-    H.init(args.hist ? args.hist + kHistPerWG * blockIdx.x : nullptr, args.p.m);
+    __shared__ double hist_uniform[HREG ? 1 : 2 * kMaxM];  // rho and alpha of a history in memory
+    H.init(args.hist ? args.hist + kHistPerWG * blockIdx.x : nullptr, hist_uniform, args.p.m);
 
     const int start = args.plan.cls[args.cls];
     const int count = args.plan.cls[kNumClasses + args.cls];

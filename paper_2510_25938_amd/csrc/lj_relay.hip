@@ -362,7 +362,7 @@ relay_kernel(MinArgs args) {
     tm.rho = args.rho;
     tm.up_n = 0;
     History<1, A, true> H;
-    H.init(nullptr, args.p.m);
+    H.init(nullptr, nullptr, args.p.m);
     const int start = args.plan.cls[args.cls];
     const int count = args.plan.cls[kNumClasses + args.cls];
     for (;;) {
