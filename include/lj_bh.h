@@ -323,17 +323,16 @@ lj_status lj_bh_step(const lj_batch* chains, const lj_bh_state* state, const lj_
  *                                 (N <= 16), 2 two clusters per wavefront
  *                                 (N <= 32), 3 four clusters per wavefront
  *                                 (N <= 16); 4-7 shapes 0-3 compiled to run
- *                                 two wavefronts per SIMD (registers capped
- *                                 at 256, the rest spilled);
- *                        class 1: w = 0 two wavefronts, 1 one wavefront with
- *                                 two atoms per lane;
+ *                                 two wavefronts per SIMD (at most 256
+ *                                 registers);
+ *                        class 1: w = 0 two wavefronts, 1 the same with the
+ *                                 FP32 pairs summed in the ordered loop;
  *                        class 2: w = 0 four wavefronts, 1 three wavefronts
  *                                 (N <= 192).
  *                      lj_set_schedule: w = -1 removes the entry (built-in
  *                      rule); a is ignored.  lj_get_schedule: *w = the entry
- *                      or -1 (none: the built-in rule, which for class 1 also
- *                      depends on the cluster count), *a = its clusters per
- *                      workgroup.
+ *                      or -1 (none: the built-in rule, which also depends on
+ *                      the cluster count), *a = its clusters per workgroup.
  * Results never depend on the schedule in LJ_FP64 (fixed summation order).
  */
 #define LJ_SCHED_EVAL 0

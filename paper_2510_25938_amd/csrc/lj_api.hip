@@ -231,22 +231,44 @@ int default_class_shape(int c, int max_n, int top_class, int mixed, int num, int
         // Two wavefronts per SIMD (registers capped, some spilled) once the
         // call holds only this class and has more wavefronts than SIMDs: the
         // second wavefront fills the first one's issue gaps (2048 x LJ38
-        // mixed: 3.85 instead of 4.39 ms; 16384 x LJ13: 1.82 instead of 2.27
+        // mixed: 3.47 instead of 4.33 ms; 16384 x LJ13: 1.82 instead of 2.27
         // ms FP64), while with one wavefront per SIMD the spills only cost.
         const long waves = ((long)num + lj::shape_clusters_per_wg(0, shape) - 1) /
                            lj::shape_clusters_per_wg(0, shape);
-        if (top_class == 0 && waves > 4L * cus) shape += 4;
+        // The mixed kernel keeps half of its history in LDS then, and wins beside
+        // class 1 too (512 chains x 8 of 38..75 atoms: 8.3 instead of 9.0 ms per
+        // step; 256 chains level).
+        if (waves > 4L * cus && (top_class == 0 || (mixed && top_class == 1 && num > 8 * cus)))
+            shape += 4;
         return shape;
     }
     if (c == 2) return cmax <= 192 ? 1 : 0; // three wavefronts
-    // Class 1 as one wavefront with two atoms per lane: about 1.5 times the
-    // time per iteration of two wavefronts, but one SIMD per team instead of
-    // two, so twice the teams drain the class.  That wins when the class
-    // shares the call with larger clusters, and on the FP64 path when the
-    // batch has at least one cluster per SIMD; otherwise the slowest cluster
-    // decides and two wavefronts are faster (mixed-path registers spill more
-    // in the one-wavefront form).
-    return (top_class >= 2 || (!mixed && num >= 4 * cus)) ? 1 : 0;
+    // Class 1 beside larger classes sums its FP32 pairs in the ordered loop
+    // (a choice of summation order, kept so that results stay what they were).
+    return top_class >= 2 ? 1 : 0;
+}
+
+// Whether the teams of classes 1 and 2 run two wavefronts per SIMD (half of the
+// history in LDS, 256 registers) or one (512 registers).  Two wavefronts fill
+// each other's issue gaps (a lone one issues FP64 every 6 and FP32 every 6
+// cycles, two together every 4.6 and 3), but a call that does not fill the chip
+// is better spread out.  The sizes are taken as uniform between
+// 2 mean - max and max.  Measured (ms, one / two wavefronts per SIMD, mixed):
+// 600, 800, 1024, 1500 and 4096 clusters of 13..150 atoms 16.1 / 18.1,
+// 16.9 / 17.1, 19.2 / 16.6, 22.7 / 17.0 and 49.6 / 31.7; 512, 640 and 2048 x LJ98
+// 11.8 / 12.3, 15.9 / 12.8 and 29.7 / 21.7; 300 and 600 of 65..250 atoms
+// 19.4 / 22.4 and 28.3 / 26.2; 256, 300 and 512 x LJ160 (one team per CU
+// otherwise) 18.3 / 17.6, 20.9 / 17.8 and 26.3 / 20.5.
+bool dense_classes(int num, int max_n, int64_t total, int cus) {
+    const double mean = (double)total / (num > 0 ? num : 1);
+    const double lo = std::max(0.0, 2.0 * mean - max_n), span = max_n - lo + 1.0;
+    const double w2 = max_n <= 192 ? 3.0 : 4.0;
+    auto share = [&](double a, double b) {  // of the sizes in (a, b]
+        return std::max(0.0, std::min(b, (double)max_n) - std::max(a, lo - 1.0)) / span;
+    };
+    const double waves =
+        num * (share(-1, 64) + 2.0 * share(64, 128) + w2 * share(128, 256) + 16.0 * share(256, 1024));
+    return waves > 1.25 * 4 * cus || (mean > 128.0 && max_n <= 256 && num > cus);
 }
 
 int class_schedule(int precision, int c, int max_n, int num, int cus) {
@@ -270,7 +292,7 @@ struct MinLayout {
 };
 
 // force (nullable): a shape per class, -1 for the schedule table's choice.
-lj_status min_layout(int num, int max_n, int mixed, int pot, MinLayout& L,
+lj_status min_layout(int num, int max_n, int64_t total, int mixed, int pot, MinLayout& L,
                      const int* force = nullptr) {
     DeviceInfo di;
     lj_status s = device_info(di);
@@ -287,8 +309,12 @@ lj_status min_layout(int num, int max_n, int mixed, int pot, MinLayout& L,
     L.top_class = lj::class_of(max_n < 0 ? 0 : max_n);
     for (int c = 0; c <= L.top_class; ++c) {
         L.shape[c] = (force && force[c] >= 0) ? force[c] : class_schedule(prec, c, max_n, num, di.cus);
+        if ((c == 1 || c == 2) && L.shape[c] < lj::class_shapes(c) &&
+            dense_classes(num, max_n, total, di.cus))
+            L.shape[c] |= lj::kDenseShape;
         if (L.shape[c] < 0 ||
-            (L.shape[c] >= lj::class_shapes(c) && L.shape[c] != lj::kRelayShape) ||
+            ((L.shape[c] & ~lj::kDenseShape) >= lj::class_shapes(c) &&
+             L.shape[c] != lj::kRelayShape) ||
             lj::shape_max_n(c, L.shape[c]) < class_cap(c, max_n))
             return fail(LJ_E_ARG, "minimiser shape %d of class %d does not hold %d atoms",
                         L.shape[c], c, class_cap(c, max_n));
@@ -473,9 +499,9 @@ lj_status bh_layout(const lj_batch* ch, const lj_bh_params* bh, int mixed, BhLay
     L.pi = take(sizeof(int32_t) * (size_t)ch->num);
     L.pv = take(sizeof(int32_t) * (size_t)ch->num);
     L.ps = take(sizeof(int32_t) * (size_t)ch->num);
-    lj_status s = min_layout(L.cand_num, ch->max_n, mixed, ch->pair, L.cand_min);
+    lj_status s = min_layout(L.cand_num, ch->max_n, L.cand_total, mixed, ch->pair, L.cand_min);
     if (s != LJ_OK) return s;
-    s = min_layout(ch->num, ch->max_n, 0, ch->pair, L.polish_min);
+    s = min_layout(ch->num, ch->max_n, ch->total_atoms, 0, ch->pair, L.polish_min);
     if (s != LJ_OK) return s;
     L.min = off;
     const size_t m = L.cand_min.total > L.polish_min.total ? L.cand_min.total : L.polish_min.total;
@@ -734,7 +760,7 @@ size_t lj_minimize_workspace_bytes(const lj_batch* batch, const lj_lbfgs_params*
     (void)params;
     if (check_batch(batch, LJ_MAX_ATOMS_MIN, "lj_minimize_workspace_bytes") != LJ_OK) return 0;
     MinLayout L;
-    if (min_layout(batch->num, batch->max_n, precision == LJ_MIXED, batch->pair, L) != LJ_OK)
+    if (min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED, batch->pair, L) != LJ_OK)
         return 0;
     return L.total;
 }
@@ -754,7 +780,7 @@ lj_status lj_bh_minimize_batch(const lj_batch* batch, double* xyz, double* energ
         return fail(LJ_E_ARG, "an output array is NULL");
     if (batch->total_atoms > 0 && !xyz) return fail(LJ_E_ARG, "xyz is NULL");
     MinLayout L;
-    if ((s = min_layout(batch->num, batch->max_n, precision == LJ_MIXED, batch->pair, L)) != LJ_OK) return s;
+    if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED, batch->pair, L)) != LJ_OK) return s;
     if (!ws || ws_bytes < L.total)
         return fail(LJ_E_WORKSPACE, "workspace of %zu bytes given, %zu needed", ws_bytes, L.total);
     return enqueue_minimize(batch, nullptr, xyz, energy, gnorm, iters, evals, status, xyz_switch,
@@ -788,7 +814,7 @@ lj_status lj_bh_minimize_batch_noalloc(const lj_batch* batch, double* xyz, doubl
                     "static scratch holds; use lj_bh_minimize_batch",
                     batch->num, LJ_NOALLOC_MAX_CLUSTERS, LJ_NOALLOC_SCRATCH_BYTES);
     MinLayout L;
-    if ((s = min_layout(batch->num, batch->max_n, precision == LJ_MIXED, batch->pair, L)) != LJ_OK)
+    if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED, batch->pair, L)) != LJ_OK)
         return s;
     if (L.total > (size_t)LJ_NOALLOC_SCRATCH_BYTES)
         return fail(LJ_E_WORKSPACE, "lj_bh_minimize_batch_noalloc: %zu bytes of scratch needed, "
@@ -978,7 +1004,7 @@ size_t lj_autotune_workspace_bytes(const lj_batch* batch, int32_t precision) {
         off = align_up(off + sizeof(double) * 3 * (size_t)batch->total_atoms);  // xyz copy
         off = align_up(off + 5 * sizeof(double) * (size_t)batch->num);          // outputs
         MinLayout L;
-        if (min_layout(batch->num, batch->max_n, precision == LJ_MIXED, batch->pair, L) != LJ_OK)
+        if (min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED, batch->pair, L) != LJ_OK)
         return 0;
         off = align_up(off + L.total);
     }
@@ -1082,15 +1108,15 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
         int32_t* ev = it + batch->num;
         int32_t* stt = ev + batch->num;
         MinLayout base;
-        if ((s = min_layout(batch->num, batch->max_n, mixed, batch->pair, base)) != LJ_OK)
+        if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, mixed, batch->pair, base)) != LJ_OK)
             return s;
         int chosen[lj::kNumClasses] = {-1, -1, -1, -1};
-        for (int c = 0; c <= base.top_class; ++c) chosen[c] = base.shape[c];
+        for (int c = 0; c <= base.top_class; ++c) chosen[c] = base.shape[c] & ~lj::kDenseShape;
         lj_lbfgs_params lp;
         lj_lbfgs_defaults(&lp);
         auto time_shapes = [&](const int* force, const lj_lbfgs_params& prm, float& ms) -> lj_status {
             MinLayout L;
-            lj_status r = min_layout(batch->num, batch->max_n, mixed, batch->pair, L, force);
+            lj_status r = min_layout(batch->num, batch->max_n, batch->total_atoms, mixed, batch->pair, L, force);
             if (r != LJ_OK) return r;
             return time_it([&]() -> lj_status {
                 LJ_HIP_TRY(hipMemcpyAsync(xc, xyz, sizeof(double) * 3 * (size_t)batch->total_atoms,
@@ -1127,7 +1153,7 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
         int32_t counts[2 * lj::kNumClasses] = {0};
         if (s == LJ_OK) {
             MinLayout L;
-            if ((s = min_layout(batch->num, batch->max_n, mixed, batch->pair, L, chosen)) != LJ_OK)
+            if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, mixed, batch->pair, L, chosen)) != LJ_OK)
                 return s;
             LJ_HIP_TRY(hipMemcpyAsync(counts, w + off + L.cls, sizeof(counts),
                                       hipMemcpyDeviceToHost, st));

@@ -102,6 +102,8 @@ size_t class_hist_bytes_per_wg(int c, int shape);
 // The form with helper wavefronts (lj_relay.hip), a shape beside the numbered
 // ones that only the built-in rule chooses.
 constexpr int kRelayShape = 16;
+// Added to a shape of class 1 or 2: its form for two wavefronts per SIMD.
+constexpr int kDenseShape = 32;
 const void* relay_kernel_for(int mixed, int pot, int c);  // nullptr: none
 int relay_block();
 const void* minimize_kernel_for(int mixed, int pot, int c, int shape);

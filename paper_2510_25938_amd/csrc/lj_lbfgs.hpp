@@ -18,7 +18,10 @@ namespace lj {
 // UP (Morse pair): the FP64 evaluation takes the unique-pair form
 // (pairs_morse64_up) for clusters of at most up_n atoms, with an up_n x up_n
 // pair matrix at upm.
-template <int W, int A, int POT, int L = kWave, int G = 1, bool UP = false>
+// TILES: FP32 evaluations above 32 atoms take the unique-pair tiles (their own
+// summation order; without, the ordered loop).
+template <int W, int A, int POT, int L = kWave, int G = 1, bool UP = false,
+          bool TILES = kUseTiles<W, A>>
 struct Team {
     static_assert(G == 1 || (W == 1 && A == 1 && L == kWave), "packing: one wavefront, one slot");
     static_assert(!UP || (W == 1 && A == 1 && G == 1 && POT == kPairMorse),
@@ -185,7 +188,7 @@ struct Team {
     // the Morse pair (e_i holds V).
     template <bool F32>
     __device__ __forceinline__ double eval(const double (&x)[3][A], double (&g)[3][A]) {
-        constexpr bool kTiles = F32 && POT == kPairLJ && kUseTiles<W, A> && G == 1;
+        constexpr bool kTiles = F32 && POT == kPairLJ && TILES && G == 1;
         constexpr bool kRing = F32 && W == 1 && A == 1 && G == 1;
         bool ring = false, tiles = false;
         if constexpr (kRing) ring = ring_for(n);
@@ -378,6 +381,131 @@ struct History<W, A, true> {
                     for (int q = 0; q < A; ++q) r[c][q] = fma(w, S[k][c][q], r[c][q]);
             }
         }
+    }
+};
+
+// One atom per lane, two wavefronts per SIMD (256 registers): the kMaxM pairs
+// take 120 registers, which the mixed kernel does not have beside its two
+// evaluations.  The KR newest pairs stay in registers by age; a push
+// hands the oldest of them to a ring in LDS, where an atom's pair is a 48-byte
+// record (three 16-byte reads per lane, which touch every bank once per eight
+// lanes), read ahead of the reductions.  With it the mixed kernels of 1, 2 and 3
+// wavefronts fit 256 registers with at most 28 bytes of scratch (302, 408 and 410
+// registers with the whole history in registers).
+template <int W, int KR>
+struct HistoryHybrid {
+    static constexpr int T = kWave * W;
+    static constexpr int R = kMaxM - KR;  // pairs in LDS
+    static constexpr int kRecord = 3;     // double2
+    static constexpr int kBytes =
+        R * T * kRecord * (int)sizeof(double2) + kMaxM * (int)sizeof(double);
+    double S[KR][3], Y[KR][3];
+    double rho[kMaxM];
+    double2* ring;  // this lane's record in slot 0
+    double* alpha;  // the recursion's alphas, equal in every lane
+    int at = 0;     // slot of age KR
+    int hist = 0;
+    double gamma = 1.0;
+
+    struct Pair {
+        double s[3][1], y[3][1];
+    };
+
+    __device__ __forceinline__ void init(char* lds) {
+        ring = reinterpret_cast<double2*>(lds) + threadIdx.x * kRecord;
+        alpha = reinterpret_cast<double*>(lds + R * T * kRecord * sizeof(double2));
+        at = 0;
+        hist = 0;
+        gamma = 1.0;
+    }
+    __device__ __forceinline__ void clear() { hist = 0; }
+
+    __device__ __forceinline__ Pair pair(int age) const {
+        Pair p;
+        if (age < KR) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                p.s[c][0] = S[age][c];
+                p.y[c][0] = Y[age][c];
+            }
+        } else {
+            int k = at - (age - KR);
+            if (k < 0) k += R;
+            const double2* q = ring + k * T * kRecord;
+            const double2 u = q[0], v = q[1], w = q[2];
+            p.s[0][0] = u.x;
+            p.s[1][0] = u.y;
+            p.s[2][0] = v.x;
+            p.y[0][0] = v.y;
+            p.y[1][0] = w.x;
+            p.y[2][0] = w.y;
+        }
+        return p;
+    }
+
+    __device__ __forceinline__ void push(const double (&s)[3][1], const double (&y)[3][1], double r,
+                                         double gam, int m) {
+        at = at + 1 == R ? 0 : at + 1;
+        double2* q = ring + at * T * kRecord;
+        q[0] = make_double2(S[KR - 1][0], S[KR - 1][1]);
+        q[1] = make_double2(S[KR - 1][2], Y[KR - 1][0]);
+        q[2] = make_double2(Y[KR - 1][1], Y[KR - 1][2]);
+#pragma unroll
+        for (int k = KR - 1; k > 0; --k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                S[k][c] = S[k - 1][c];
+                Y[k][c] = Y[k - 1][c];
+            }
+#pragma unroll
+        for (int k = kMaxM - 1; k > 0; --k) rho[k] = rho[k - 1];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            S[0][c] = s[c][0];
+            Y[0][c] = y[c][0];
+        }
+        rho[0] = r;
+        gamma = gam;
+        hist = hist < m ? hist + 1 : m;
+    }
+
+    template <bool FULL, class TM>
+    __device__ __forceinline__ void apply_n(TM& tm, double (&r)[3][1], int h) {
+        Pair ahead = pair(KR);  // the pair of age KR, ahead of its turn
+#pragma unroll
+        for (int k = 0; k < kMaxM; ++k) {
+            if (FULL || k < h) {
+                const Pair p = k < KR ? pair(k) : ahead;
+                if (k >= KR && k + 1 < kMaxM) ahead = pair(k + 1);
+                const double a = rho[k] * tm.dot(p.s, r);
+                alpha[k] = a;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) r[c][0] = fma(-a, p.y[c][0], r[c][0]);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) r[c][0] = gamma * r[c][0];
+        if (FULL || h > KR) ahead = pair(FULL ? kMaxM - 1 : h - 1);
+#pragma unroll
+        for (int k = kMaxM - 1; k >= 0; --k) {
+            if (FULL || k < h) {
+                const Pair p = k < KR ? pair(k) : ahead;
+                if (k > KR) ahead = pair(k - 1);
+                const double b = rho[k] * tm.dot(p.y, r);
+                const double w = alpha[k] - b;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) r[c][0] = fma(w, p.s[c][0], r[c][0]);
+            }
+        }
+    }
+
+    template <class TM>
+    __device__ __forceinline__ void apply(TM& tm, double (&r)[3][1]) {
+        const int h = tm.uni(hist);
+        if (h == kMaxM)
+            apply_n<true>(tm, r, h);
+        else if (h > 0)
+            apply_n<false>(tm, r, h);
     }
 };
 

@@ -14,9 +14,13 @@
 // (the size classes run concurrently on side streams).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "lj_lbfgs.hpp"
 
 namespace lj {
+
+constexpr int kHybridRegs = 5;
 
 // ---------------------------------------------------------------------------
 // Persistent minimiser kernel: one launch per size class.  A workgroup claims
@@ -24,7 +28,8 @@ namespace lj {
 // one per packed team of 64 / G lanes) and minimises it; it claims again once
 // all of its teams are done.
 // ---------------------------------------------------------------------------
-template <int MIXED, int W, int A, bool HREG, int POT, int L = kWave, int G = 1, int OCC = 1>
+template <int MIXED, int W, int A, bool HREG, int POT, int L = kWave, int G = 1, int OCC = 1,
+          bool TILES = kUseTiles<W, A>>
 __global__ __launch_bounds__(kWave* W) __attribute__((amdgpu_waves_per_eu(OCC))) void minimize_kernel(
     MinArgs args) {
     constexpr int T = kWave * W;
@@ -33,7 +38,7 @@ __global__ __launch_bounds__(kWave* W) __attribute__((amdgpu_waves_per_eu(OCC)))
     __shared__ TeamScratch<W, 4 * A> scratch;
     __shared__ int claim;
     __shared__ float tile_rbuf[(MIXED && G == 1 &&
-                                ((POT == kPairLJ && kUseTiles<W, A>) || (W == 1 && A == 1)))
+                                ((POT == kPairLJ && TILES) || (W == 1 && A == 1)))
                                    ? 6 * T * A
                                    : 1];
 
@@ -44,7 +49,7 @@ __global__ __launch_bounds__(kWave* W) __attribute__((amdgpu_waves_per_eu(OCC)))
     constexpr bool kUp = W == 1 && A == 1 && G == 1 && OCC == 1 && POT == kPairMorse;
     extern __shared__ double2 up_matrix[];
     const int team = G > 1 ? (int)threadIdx.x / LG : 0;
-    Team<W, A, POT, L, G, kUp> tm;
+    Team<W, A, POT, L, G, kUp, TILES> tm;
     tm.upm = up_matrix;
     tm.up_n = kUp ? args.up_n : 0;
     tm.uplist = reinterpret_cast<uint2*>(up_matrix + (size_t)tm.up_n * tm.up_n);
@@ -55,10 +60,18 @@ __global__ __launch_bounds__(kWave* W) __attribute__((amdgpu_waves_per_eu(OCC)))
     tm.sc = &scratch;
     tm.bank = 0;
     tm.rho = args.rho;
-    History<W, A, HREG> H;
-    constexpr size_t kHistPerWG = (size_t)2 * kMaxM * 3 * A * T;
+    // kernels at two wavefronts per SIMD whose registers do not hold the history
+    // keep half of it in LDS
+    constexpr bool kHybrid = HREG && A == 1 && G == 1 && OCC == 2 && (MIXED || W > 1);
+    typename std::conditional<kHybrid, HistoryHybrid<W, kHybridRegs>, History<W, A, HREG>>::type H;
     __shared__ double hist_uniform[HREG ? 1 : 2 * kMaxM];  // rho and alpha of a history in memory
-    H.init(args.hist ? args.hist + kHistPerWG * blockIdx.x : nullptr, hist_uniform, args.p.m);
+    __shared__ __align__(16) char hist_ring[kHybrid ? HistoryHybrid<W, kHybridRegs>::kBytes : 16];
+    if constexpr (kHybrid) {
+        H.init(hist_ring);
+    } else {
+        constexpr size_t kHistPerWG = (size_t)2 * kMaxM * 3 * A * T;
+        H.init(args.hist ? args.hist + kHistPerWG * blockIdx.x : nullptr, hist_uniform, args.p.m);
+    }
 
     const int start = args.plan.cls[args.cls];
     const int count = args.plan.cls[kNumClasses + args.cls];
@@ -259,8 +272,11 @@ hipError_t launch_energy_grad(int mixed, int pot, EvalShape s, int num, const in
 //                        4-7  shapes 0-3 compiled for two wavefronts per SIMD
 //                           (at most 256 registers, the rest spilled): for
 //                           batches of more wavefronts than SIMDs
-//   class 1 (N <= 128):  0  two wavefronts;  1  one wavefront, two atoms per lane
+//   class 1 (N <= 128):  0  two wavefronts;  1  the same with FP32 pairs summed
+//                           in the ordered loop
 //   class 2 (N <= 256):  0  four wavefronts;  1  three wavefronts (N <= 192)
+//                        (classes 1 and 2: compiled for one and for two
+//                        wavefronts per SIMD, kDenseShape added to the number)
 //   class 3 (N <= 1024): 0  16 wavefronts x 1 atom, 1  8 x 2, 2  4 x 4
 struct ClassShape {
     int W, A;
@@ -273,15 +289,18 @@ constexpr int kShapes[kNumClasses] = {8, 2, 2, 3};
 constexpr ClassShape kShape[kNumClasses][kMaxShapes] = {
     {{1, 1, true, 1, 64}, {1, 1, true, 1, 16}, {1, 1, true, 2, 32}, {1, 1, true, 4, 16},
      {1, 1, true, 1, 64}, {1, 1, true, 1, 16}, {1, 1, true, 2, 32}, {1, 1, true, 4, 16}},
-    {{2, 1, true, 1, 128}, {1, 2, true, 1, 128}},
+    {{2, 1, true, 1, 128}, {2, 1, true, 1, 128}},
     {{4, 1, true, 1, 256}, {3, 1, true, 1, 192}},
     {{16, 1, false, 1, 1024}, {8, 2, false, 1, 1024}, {4, 4, false, 1, 1024}}};
 
 int class_shapes(int c) { return c >= 0 && c < kNumClasses ? kShapes[c] : 0; }
+static const ClassShape& shape_of(int c, int shape) { return kShape[c][shape & ~kDenseShape]; }
 int shape_max_n(int c, int shape) {
-    return shape == kRelayShape ? kClassMaxN[c] : kShape[c][shape].max_n;
+    return shape == kRelayShape ? kClassMaxN[c] : shape_of(c, shape).max_n;
 }
-int shape_clusters_per_wg(int c, int shape) { return shape == kRelayShape ? 1 : kShape[c][shape].G; }
+int shape_clusters_per_wg(int c, int shape) {
+    return shape == kRelayShape ? 1 : shape_of(c, shape).G;
+}
 
 int class_of(int n) {
     for (int c = 0; c < kNumClasses; ++c)
@@ -291,17 +310,29 @@ int class_of(int n) {
 
 size_t class_hist_bytes_per_wg(int c, int shape) {
     if (shape == kRelayShape) return 0;
-    const ClassShape s = kShape[c][shape];
+    const ClassShape s = shape_of(c, shape);
     return s.hreg ? 0 : (size_t)2 * kMaxM * 3 * s.A * kWave * s.W * sizeof(double);
 }
 
-template <int MIXED, int W, int A, bool HREG, int POT, int L = kWave, int G = 1, int OCC = 1>
+template <int MIXED, int W, int A, bool HREG, int POT, int L = kWave, int G = 1, int OCC = 1,
+          bool TILES = kUseTiles<W, A>>
 static const void* min_kernel_ptr() {
-    return reinterpret_cast<const void*>(&minimize_kernel<MIXED, W, A, HREG, POT, L, G, OCC>);
+    return reinterpret_cast<const void*>(
+        &minimize_kernel<MIXED, W, A, HREG, POT, L, G, OCC, TILES>);
 }
 
 template <int MIXED, int POT>
 static const void* minimize_kernel_pm(int c, int shape) {
+    if (shape & kDenseShape) {
+        switch (c * kMaxShapes + (shape & ~kDenseShape)) {
+            case kMaxShapes + 0: return min_kernel_ptr<MIXED, 2, 1, true, POT, kWave, 1, 2>();
+            case kMaxShapes + 1:
+                return min_kernel_ptr<MIXED, 2, 1, true, POT, kWave, 1, 2, MIXED == 0>();
+            case 2 * kMaxShapes + 0: return min_kernel_ptr<MIXED, 4, 1, true, POT, kWave, 1, 2>();
+            case 2 * kMaxShapes + 1: return min_kernel_ptr<MIXED, 3, 1, true, POT, kWave, 1, 2>();
+        }
+        return nullptr;
+    }
     switch (c * kMaxShapes + shape) {
         case 0: return min_kernel_ptr<MIXED, 1, 1, true, POT>();
         case 1: return min_kernel_ptr<MIXED, 1, 1, true, POT, 16>();
@@ -312,7 +343,8 @@ static const void* minimize_kernel_pm(int c, int shape) {
         case 6: return min_kernel_ptr<MIXED, 1, 1, true, POT, kWave, 2, 2>();
         case 7: return min_kernel_ptr<MIXED, 1, 1, true, POT, kWave, 4, 2>();
         case kMaxShapes + 0: return min_kernel_ptr<MIXED, 2, 1, true, POT>();
-        case kMaxShapes + 1: return min_kernel_ptr<MIXED, 1, 2, true, POT>();
+        case kMaxShapes + 1:
+            return min_kernel_ptr<MIXED, 2, 1, true, POT, kWave, 1, 1, MIXED == 0>();
         case 2 * kMaxShapes + 0: return min_kernel_ptr<MIXED, 4, 1, true, POT>();
         case 2 * kMaxShapes + 1: return min_kernel_ptr<MIXED, 3, 1, true, POT>();
         case 3 * kMaxShapes + 0: return min_kernel_ptr<MIXED, 16, 1, false, POT>();
@@ -324,7 +356,8 @@ static const void* minimize_kernel_pm(int c, int shape) {
 
 const void* minimize_kernel_for(int mixed, int pot, int c, int shape) {
     if (shape == kRelayShape) return relay_kernel_for(mixed, pot, c);
-    if (c < 0 || c >= kNumClasses || shape < 0 || shape >= kShapes[c]) return nullptr;
+    if (c < 0 || c >= kNumClasses || shape < 0 || (shape & ~kDenseShape) >= kShapes[c])
+        return nullptr;
     if (pot == kPairMorse)
         return mixed ? minimize_kernel_pm<1, kPairMorse>(c, shape)
                      : minimize_kernel_pm<0, kPairMorse>(c, shape);
@@ -332,7 +365,7 @@ const void* minimize_kernel_for(int mixed, int pot, int c, int shape) {
 }
 
 int class_block(int c, int shape) {
-    return shape == kRelayShape ? relay_block() : kWave * kShape[c][shape].W;
+    return shape == kRelayShape ? relay_block() : kWave * shape_of(c, shape).W;
 }
 
 int class_up_n(int c, int shape, int max_n, int pot) {
