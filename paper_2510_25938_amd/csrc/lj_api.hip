@@ -203,8 +203,9 @@ std::array<int, 4> class_key(int precision, int c, int max_n) {
             pow2_at_least(class_cap(c, max_n) < 1 ? 1 : class_cap(c, max_n))};
 }
 
-// Built-in rule for the shape of class c (0-2).
-int default_class_shape(int c, int max_n, int top_class, int mixed, int num, int cus) {
+// Built-in rule for the shape of class c (0-2); mean: the batch's mean size.
+int default_class_shape(int c, int max_n, int top_class, int mixed, int pot, int num, double mean,
+                        int cus) {
     const int cmax = class_cap(c, max_n);
     // Helper wavefronts (FP64) while every cluster's workgroup is resident at
     // once, so that they run on SIMDs which would idle: two workgroups per CU
@@ -217,30 +218,44 @@ int default_class_shape(int c, int max_n, int top_class, int mixed, int num, int
     if (!mixed && c <= 1 && cmax >= 20 && num <= (c == 0 && top_class == 0 ? 2 : 1) * cus)
         return lj::kRelayShape;
     if (c == 0) {
-        // Several clusters per wavefront once the batch has more than two
-        // clusters per SIMD: each wavefront then does the work of two or four
-        // (16384 x LJ13: 1.75 instead of 4.2 ms, FP64); below that the batch
-        // waits for its slowest cluster, and a packed wavefront waits for the
-        // slowest of its clusters, so one cluster per wavefront is as fast.
+        // Several clusters per wavefront once the batch has more than one
+        // cluster per SIMD: each wavefront then does the work of two or four
+        // (2048 x LJ13 FP64 0.76 instead of 0.88 ms, mixed 0.74 instead of
+        // 0.97; 2048 x LJ30 2.28 instead of 2.90; 16384 x LJ13 1.76 instead of
+        // 4.2).  Up to two clusters per SIMD only where the sizes are much
+        // alike, since a packed wavefront waits for the slowest of its clusters
+        // (2048 of 4..16 atoms: 0.98 instead of 0.91 ms).  Above 16 atoms in
+        // FP64 and beyond two clusters per SIMD alone: the mixed path's packed
+        // teams sum 20 atoms and more in another order.  The Morse pair's
+        // one-cluster kernel evaluates unique pairs, the packed ones do not
+        // (2048 x Morse13 FP64: 1.44 packed, 1.45 not, mixed, where only the
+        // polish loses, 1.03 and 1.1; 2048 x Morse30 FP64: 4.7 and 4.3).
         const bool many = num > 2 * 4 * cus;
+        const bool alike =
+            (pot == LJ_PAIR_LJ || mixed) && num > 4 * cus && mean > 0.7 * cmax;
         int shape = 0;
         if (cmax <= 16)
-            shape = many ? 3 : 1;
-        else if (cmax <= 32 && many)
+            shape = many || alike ? 3 : 1;
+        else if (cmax <= 32 && (many || (alike && !mixed)))
             shape = 2;
-        // Two wavefronts per SIMD (registers capped, some spilled) once the
-        // call holds only this class and has more wavefronts than SIMDs: the
-        // second wavefront fills the first one's issue gaps (2048 x LJ38
-        // mixed: 3.47 instead of 4.33 ms; 16384 x LJ13: 1.82 instead of 2.27
-        // ms FP64), while with one wavefront per SIMD the spills only cost.
-        const long waves = ((long)num + lj::shape_clusters_per_wg(0, shape) - 1) /
-                           lj::shape_clusters_per_wg(0, shape);
-        // The mixed kernel keeps half of its history in LDS then, and wins beside
-        // class 1 too (512 chains x 8 of 38..75 atoms: 8.3 instead of 9.0 ms per
-        // step; 256 chains level).
-        if (waves > 4L * cus && (top_class == 0 || (mixed && top_class == 1 && num > 8 * cus)))
-            shape += 4;
-        return shape;
+        // Two wavefronts per SIMD (at most 256 registers) once the call has more
+        // wavefronts than SIMDs: the second wavefront fills the first one's
+        // issue gaps (2048 x LJ38 mixed 3.47 instead of 4.33 ms; 16384 x LJ13
+        // FP64 1.76 instead of 2.27).  The mixed kernel keeps half of its
+        // history in LDS then, and wins beside class 1 too (512 chains x 8 of
+        // 38..75 atoms: 8.3 instead of 9.0 ms per step; 256 chains level).
+        // Morse pair: not where that ends the unique-pair evaluation (up to 40
+        // atoms, one cluster per wavefront: 2048 x Morse38 FP64 7.4 instead of
+        // 9.1 ms, 3000 of 20..60 atoms 14.4 instead of 16.7, but 4096 x Morse60
+        // 35.8 instead of 32.0; mixed, where only the polish loses, 8192 x
+        // Morse38 13.7 instead of 11.1), nor for the packed mixed kernel, which
+        // spills (16384 x Morse13 2.96 instead of 3.6 ms).
+        const long per_wg = lj::shape_clusters_per_wg(0, shape);
+        const long waves = ((long)num + per_wg - 1) / per_wg;
+        bool two = waves > 4L * cus && (top_class == 0 || (mixed && top_class == 1 && num > 8 * cus));
+        if (pot == LJ_PAIR_MORSE)
+            two = two && (per_wg > 1 ? !mixed : mean > 40.0 || (mixed && waves > 16L * cus));
+        return two ? shape + 4 : shape;
     }
     if (c == 2) return cmax <= 192 ? 1 : 0; // three wavefronts
     // Class 1 beside larger classes sums its FP32 pairs in the ordered loop
@@ -259,8 +274,7 @@ int default_class_shape(int c, int max_n, int top_class, int mixed, int num, int
 // 11.8 / 12.3, 15.9 / 12.8 and 29.7 / 21.7; 300 and 600 of 65..250 atoms
 // 19.4 / 22.4 and 28.3 / 26.2; 256, 300 and 512 x LJ160 (one team per CU
 // otherwise) 18.3 / 17.6, 20.9 / 17.8 and 26.3 / 20.5.
-bool dense_classes(int num, int max_n, int64_t total, int cus) {
-    const double mean = (double)total / (num > 0 ? num : 1);
+bool dense_classes(int num, int max_n, double mean, int cus) {
     const double lo = std::max(0.0, 2.0 * mean - max_n), span = max_n - lo + 1.0;
     const double w2 = max_n <= 192 ? 3.0 : 4.0;
     auto share = [&](double a, double b) {  // of the sizes in (a, b]
@@ -271,7 +285,7 @@ bool dense_classes(int num, int max_n, int64_t total, int cus) {
     return waves > 1.25 * 4 * cus || (mean > 128.0 && max_n <= 256 && num > cus);
 }
 
-int class_schedule(int precision, int c, int max_n, int num, int cus) {
+int class_schedule(int precision, int c, int max_n, int pot, int num, double mean, int cus) {
     const int top = lj::class_of(max_n < 0 ? 0 : max_n);
     if (c == 3) return large_schedule(precision);
     {
@@ -280,7 +294,7 @@ int class_schedule(int precision, int c, int max_n, int num, int cus) {
         if (it != g_class_sched.end() && lj::shape_max_n(c, it->second) >= class_cap(c, max_n))
             return it->second;
     }
-    return default_class_shape(c, max_n, top, precision == LJ_MIXED, num, cus);
+    return default_class_shape(c, max_n, top, precision == LJ_MIXED, pot, num, mean, cus);
 }
 
 // Workspace carve-up of one minimisation call, and the shape of each class.
@@ -307,10 +321,13 @@ lj_status min_layout(int num, int max_n, int64_t total, int mixed, int pot, MinL
     off = align_up(off + sizeof(int32_t) * lj::kNumClasses);
     // the plan rejects clusters above max_n, so max_n bounds every class
     L.top_class = lj::class_of(max_n < 0 ? 0 : max_n);
+    const double mean = (double)total / (num > 0 ? num : 1);
     for (int c = 0; c <= L.top_class; ++c) {
-        L.shape[c] = (force && force[c] >= 0) ? force[c] : class_schedule(prec, c, max_n, num, di.cus);
+        L.shape[c] = (force && force[c] >= 0)
+                         ? force[c]
+                         : class_schedule(prec, c, max_n, pot, num, mean, di.cus);
         if ((c == 1 || c == 2) && L.shape[c] < lj::class_shapes(c) &&
-            dense_classes(num, max_n, total, di.cus))
+            dense_classes(num, max_n, mean, di.cus))
             L.shape[c] |= lj::kDenseShape;
         if (L.shape[c] < 0 ||
             ((L.shape[c] & ~lj::kDenseShape) >= lj::class_shapes(c) &&
