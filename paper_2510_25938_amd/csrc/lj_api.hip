@@ -217,6 +217,11 @@ int default_class_shape(int c, int max_n, int top_class, int mixed, int pot, int
     // iteration, LJ20 3.86 instead of 3.97 us).
     if (!mixed && c <= 1 && cmax >= 20 && num <= (c == 0 && top_class == 0 ? 2 : 1) * cus)
         return lj::kRelayShape;
+    // Two wavefronts per cluster up to one cluster per SIMD (Eq. (1), class 0):
+    // 1024, 800 and 600 x LJ38 2.9, 2.6 and 2.6 instead of 3.2, 3.0 and 3.0 ms,
+    // 1024 x LJ64 5.2 instead of 5.7, 1024 x LJ24 1.60 instead of 1.66.
+    if (!mixed && pot == LJ_PAIR_LJ && c == 0 && top_class == 0 && cmax >= 20 && num <= 4 * cus)
+        return lj::kRelayPairShape;
     if (c == 0) {
         // Several clusters per wavefront once the batch has more than one
         // cluster per SIMD: each wavefront then does the work of two or four
@@ -331,7 +336,7 @@ lj_status min_layout(int num, int max_n, int64_t total, int mixed, int pot, MinL
             L.shape[c] |= lj::kDenseShape;
         if (L.shape[c] < 0 ||
             ((L.shape[c] & ~lj::kDenseShape) >= lj::class_shapes(c) &&
-             L.shape[c] != lj::kRelayShape) ||
+             !lj::is_relay(L.shape[c])) ||
             lj::shape_max_n(c, L.shape[c]) < class_cap(c, max_n))
             return fail(LJ_E_ARG, "minimiser shape %d of class %d does not hold %d atoms",
                         L.shape[c], c, class_cap(c, max_n));
@@ -1195,7 +1200,7 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
                 // the form with helper wavefronts has no number in the table:
                 // where it stays fastest, the built-in rule stays in charge
                 std::lock_guard<std::mutex> lk(g_sched_mu);
-                if (chosen[c] == lj::kRelayShape)
+                if (lj::is_relay(chosen[c]))
                     g_class_sched.erase(class_key(precision, c, batch->max_n));
                 else
                     g_class_sched[class_key(precision, c, batch->max_n)] = chosen[c];

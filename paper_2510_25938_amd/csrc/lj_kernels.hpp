@@ -99,13 +99,18 @@ constexpr int kUpMaxN = 40;
 int class_up_n(int c, int shape, int max_n, int pot);
 size_t class_dyn_lds(int c, int shape, int max_n, int pot);
 size_t class_hist_bytes_per_wg(int c, int shape);
-// The form with helper wavefronts (lj_relay.hip), a shape beside the numbered
-// ones that only the built-in rule chooses.
+// The forms with helper wavefronts (lj_relay.hip; four wavefronts per cluster,
+// or two), shapes beside the numbered ones that only the built-in rule chooses.
 constexpr int kRelayShape = 16;
+constexpr int kRelayPairShape = 17;
+inline bool is_relay(int shape) { return shape == kRelayShape || shape == kRelayPairShape; }
+// nullptr where there is none: FP64, classes 0 and 1 (two wavefronts: class 0, Eq. (1)).
+const void* relay_kernel_for(int mixed, int pot, int c, int shape);
+int relay_block(int shape);
 // Added to a shape of class 1 or 2: its form for two wavefronts per SIMD.
 constexpr int kDenseShape = 32;
-const void* relay_kernel_for(int mixed, int pot, int c);  // nullptr: none
-int relay_block();
+const void* relay_kernel_for(int mixed, int pot, int c, int shape);  // nullptr: none
+int relay_block(int shape);
 const void* minimize_kernel_for(int mixed, int pot, int c, int shape);
 hipError_t launch_plan(const int32_t* offset, int num, int max_n, const int32_t* active, Plan plan,
                        int32_t* status, hipStream_t st);

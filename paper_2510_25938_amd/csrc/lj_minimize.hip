@@ -296,10 +296,10 @@ constexpr ClassShape kShape[kNumClasses][kMaxShapes] = {
 int class_shapes(int c) { return c >= 0 && c < kNumClasses ? kShapes[c] : 0; }
 static const ClassShape& shape_of(int c, int shape) { return kShape[c][shape & ~kDenseShape]; }
 int shape_max_n(int c, int shape) {
-    return shape == kRelayShape ? kClassMaxN[c] : shape_of(c, shape).max_n;
+    return is_relay(shape) ? kClassMaxN[c] : shape_of(c, shape).max_n;
 }
 int shape_clusters_per_wg(int c, int shape) {
-    return shape == kRelayShape ? 1 : shape_of(c, shape).G;
+    return is_relay(shape) ? 1 : shape_of(c, shape).G;
 }
 
 int class_of(int n) {
@@ -309,7 +309,7 @@ int class_of(int n) {
 }
 
 size_t class_hist_bytes_per_wg(int c, int shape) {
-    if (shape == kRelayShape) return 0;
+    if (is_relay(shape)) return 0;
     const ClassShape s = shape_of(c, shape);
     return s.hreg ? 0 : (size_t)2 * kMaxM * 3 * s.A * kWave * s.W * sizeof(double);
 }
@@ -355,7 +355,7 @@ static const void* minimize_kernel_pm(int c, int shape) {
 }
 
 const void* minimize_kernel_for(int mixed, int pot, int c, int shape) {
-    if (shape == kRelayShape) return relay_kernel_for(mixed, pot, c);
+    if (is_relay(shape)) return relay_kernel_for(mixed, pot, c, shape);
     if (c < 0 || c >= kNumClasses || shape < 0 || (shape & ~kDenseShape) >= kShapes[c])
         return nullptr;
     if (pot == kPairMorse)
@@ -365,7 +365,7 @@ const void* minimize_kernel_for(int mixed, int pot, int c, int shape) {
 }
 
 int class_block(int c, int shape) {
-    return shape == kRelayShape ? relay_block() : kWave * shape_of(c, shape).W;
+    return is_relay(shape) ? relay_block(shape) : kWave * shape_of(c, shape).W;
 }
 
 int class_up_n(int c, int shape, int max_n, int pot) {

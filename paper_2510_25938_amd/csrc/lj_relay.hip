@@ -5,8 +5,8 @@
 // dependences, so a call of few clusters is bound by the instruction count of
 // one wavefront: about half of it the ordered pair loop, the rest the L-BFGS
 // recursion, which is serial.  Here wavefront 0 (the leader) runs the L-BFGS
-// loop with its history in registers, and three more wavefronts, on the CU's
-// other SIMDs, share the pair loop.  Its sums have a fixed order (partners
+// loop with its history in registers, and one or three more wavefronts, on the
+// CU's other SIMDs, share the pair loop.  Its sums have a fixed order (partners
 // ascending), so the partners are cut into consecutive segments: every
 // wavefront forms the terms of its segment at once, in registers, and the
 // per-atom sums are then handed from segment to segment through LDS, each
@@ -14,15 +14,15 @@
 // single-wavefront loop in the same order, so results are bitwise equal.
 //
 // Measured, us per L-BFGS iteration: LJ38 5.1 -> 4.1, LJ64 6.7 -> 4.7, LJ98
-// 12.0 -> 9.9, Morse38 6.9 -> 5.4, Morse98 25.4 -> 17.6.  The history in LDS
+// 12.0 -> 9.9, Morse38 6.9 -> 5.4, Morse98 25.4 -> 17.6 (four wavefronts); 1024 x
+// LJ38 3.2 -> 2.9 ms, 1024 x LJ64 5.7 -> 5.2 ms (two, with one workgroup's
+// wavefronts filling the issue gaps of another's).  The history in LDS
 // instead of the leader's registers cost 0.3-0.6 us per iteration.
 #include <hip/hip_runtime.h>
 
 #include "lj_lbfgs.hpp"
 
 namespace lj {
-
-constexpr int kRelayW = 4;  // wavefronts per workgroup: one per SIMD, 512 registers each
 
 // What the leader asks of the other wavefronts at an evaluation's first barrier.
 enum RelayCmd { kRelayEval = 0, kRelayEvalIeee, kRelayNew, kRelayExit };
@@ -38,15 +38,19 @@ struct RelayLds {
 // wavefront's terms are ready when its predecessor hands over: with t
 // instructions per term (21 for Eq. (1), about 70 for the Morse pair), 4 per
 // term for the sums and about 35 for an exchange,
-// n_1 t = n_0 (t + 4) + 35 and n_{s+1} t = n_s (t + 4) + 35.
-template <int S, int POT>
+// n_1 t = n_0 (t + 4) + 35 and n_{s+1} t = n_s (t + 4) + 35.  Two segments of one
+// tile: the second is at most the 20 terms that a helper's registers hold (64
+// atoms, 30 in the second: 1024 x LJ64 5.8 instead of 5.2 ms).
+template <int S, int POT, int A = 1>
 __device__ __forceinline__ int relay_cut(int s, int n) {
     static_assert(S == 2 || S == 4, "2 or 4 segments");
     if (s <= 0) return 0;
     if (s >= S) return n;
     int v;
     if constexpr (S == 2)
-        v = POT == kPairMorse ? 31 * n - 16 : 29 * n - 48;
+        v = POT == kPairMorse ? 31 * n - 16
+            : A == 1          ? max(29 * n - 48, 64 * (n - 20))
+                              : 29 * n - 48;
     else if (POT == kPairMorse)
         v = s == 1 ? 15 * n - 45 : s == 2 ? 30 * n - 62 : 47 * n - 48;
     else
@@ -90,10 +94,10 @@ __device__ __forceinline__ void relay_first(RelayLds<A>& lds, int j1, int tile, 
 // while it adds them).  Entered with an evaluation's first barrier passed;
 // serves evaluations until the leader asks for something else, and returns
 // that.
-template <int POT, bool IEEE, int NG>
+template <int W, int POT, bool IEEE, int NG>
 __device__ __forceinline__ int relay_helper(RelayLds<1>& lds, int n, int seg, int lane,
                                             double rho) {
-    constexpr int S = kRelayW;
+    constexpr int S = W;
     constexpr int CAP = kGroup64 * NG;
     const int j0 = relay_cut<S, POT>(seg, n), cnt = relay_cut<S, POT>(seg + 1, n) - j0;
     const int last = cnt > 0 ? cnt - 1 : 0;
@@ -164,8 +168,8 @@ constexpr int kRelayTerms = 72;
 template <int POT, bool IEEE>
 __device__ __forceinline__ int relay_helper2(RelayLds<2>& lds, double2* __restrict__ terms, int n,
                                              int tile, int seg, int lane, double rho) {
-    constexpr int S = kRelayW / 2;
-    const int j0 = relay_cut<S, POT>(seg, n), j1 = relay_cut<S, POT>(seg + 1, n);
+    constexpr int S = 2;  // four wavefronts, two tiles
+    const int j0 = relay_cut<S, POT, 2>(seg, n), j1 = relay_cut<S, POT, 2>(seg + 1, n);
     const int own = tile * kWave + lane;
     const double c = -2.0 * rho;
     double k24, km48;
@@ -235,12 +239,12 @@ __device__ __forceinline__ int relay_helper2(RelayLds<2>& lds, double2* __restri
     }
 }
 
-// Wavefronts 1 .. 3 until the leader is done.  role: tile role mod A, segment
+// Every wavefront but the leader, until the leader is done.  role: tile role mod A, segment
 // role / A.
-template <int A, int POT>
+template <int A, int W, int POT>
 __device__ __forceinline__ void relay_helpers(RelayLds<A>& lds, double2* terms, int role, int lane,
                                               double rho) {
-    constexpr int S = kRelayW / A;
+    constexpr int S = W / A;
     const int seg = role / A;
     int n = 0;
     __syncthreads();
@@ -257,27 +261,27 @@ __device__ __forceinline__ void relay_helpers(RelayLds<A>& lds, double2* terms, 
                       ? relay_helper2<POT, false>(lds, own, n, role % A, seg, lane, rho)
                       : relay_helper2<POT, true>(lds, own, n, role % A, seg, lane, rho);
         } else if (cmd == kRelayEvalIeee) {
-            cmd = relay_helper<POT, true, 1>(lds, n, seg, lane, rho);
+            cmd = relay_helper<W, POT, true, 1>(lds, n, seg, lane, rho);
         } else {
             // the fewest groups that hold the segment
             const int cnt = relay_cut<S, POT>(seg + 1, n) - relay_cut<S, POT>(seg, n);
             if (cnt <= 4)
-                cmd = relay_helper<POT, false, 1>(lds, n, seg, lane, rho);
+                cmd = relay_helper<W, POT, false, 1>(lds, n, seg, lane, rho);
             else if (cnt <= 8)
-                cmd = relay_helper<POT, false, 2>(lds, n, seg, lane, rho);
+                cmd = relay_helper<W, POT, false, 2>(lds, n, seg, lane, rho);
             else if (cnt <= 12)
-                cmd = relay_helper<POT, false, 3>(lds, n, seg, lane, rho);
+                cmd = relay_helper<W, POT, false, 3>(lds, n, seg, lane, rho);
             else if (cnt <= 16)
-                cmd = relay_helper<POT, false, 4>(lds, n, seg, lane, rho);
+                cmd = relay_helper<W, POT, false, 4>(lds, n, seg, lane, rho);
             else
-                cmd = relay_helper<POT, false, 5>(lds, n, seg, lane, rho);
+                cmd = relay_helper<W, POT, false, 5>(lds, n, seg, lane, rho);
         }
     }
 }
 
 // The leader's team: one wavefront with A atoms per lane, its evaluation
 // shared with the workgroup's other wavefronts.
-template <int A, int POT>
+template <int A, int W, int POT>
 struct RelayTeam : Team<1, A, POT> {
     RelayLds<A>* lds;
 
@@ -320,14 +324,14 @@ struct RelayTeam : Team<1, A, POT> {
     template <bool IEEE>
     __device__ __forceinline__ void share(const double (&x)[3][A], double (&e)[A],
                                           double (&g)[3][A]) {
-        constexpr int S = kRelayW / A;
+        constexpr int S = W / A;
         const int lane = this->li;
         if (lane == 0) lds->cmd = IEEE ? kRelayEvalIeee : kRelayEval;
         __syncthreads();
         double k24, km48;
         hold_constants(k24, km48);
         const double x0[3][1] = {{x[0][0]}, {x[1][0]}, {x[2][0]}};
-        relay_first<A, POT, IEEE>(*lds, relay_cut<S, POT>(1, this->n), 0, lane, x0, this->rho,
+        relay_first<A, POT, IEEE>(*lds, relay_cut<S, POT, A>(1, this->n), 0, lane, x0, this->rho,
                                   -2.0 * this->rho, k24, km48);
         relay_wait_rest<S>(0);
 #pragma unroll
@@ -342,20 +346,25 @@ struct RelayTeam : Team<1, A, POT> {
     }
 };
 
-// Two workgroups per CU for one-tile clusters (256 registers), one for two-tile
+// Two wavefronts per SIMD for one-tile clusters (256 registers), one for two-tile
 // clusters (the leader's history alone takes 240).
-template <int A, int POT>
-__global__ __launch_bounds__(kWave* kRelayW) __attribute__((amdgpu_waves_per_eu(A == 1 ? 2 : 1))) void
+template <int A, int W, int POT>
+__global__ __launch_bounds__(kWave* W) __attribute__((amdgpu_waves_per_eu(A == 1 ? 2 : 1))) void
 relay_kernel(MinArgs args) {
     __shared__ RelayLds<A> lds;
     __shared__ double2 terms[A == 2 ? 2 * kRelayTerms * kWave : 1];
     const int lane = threadIdx.x % kWave;
-    const int role = uniform((int)threadIdx.x / kWave);
+    int role = uniform((int)threadIdx.x / kWave);
+    // two wavefronts: four workgroups share a CU, and in every other workgroup of
+    // an XCD (consecutive workgroups go to the eight XCDs in turn) the second
+    // wavefront leads, so that leaders are spread over the SIMDs (1024 x LJ38:
+    // 2.88 instead of 2.95 ms)
+    if (W == 2) role ^= (int)(blockIdx.x >> 3) & 1;
     if (role != 0) {
-        relay_helpers<A, POT>(lds, terms, role, lane, args.rho);
+        relay_helpers<A, W, POT>(lds, terms, role, lane, args.rho);
         return;
     }
-    RelayTeam<A, POT> tm;
+    RelayTeam<A, W, POT> tm;
     tm.lds = &lds;
     tm.li = lane;
     tm.bank = 0;
@@ -379,13 +388,16 @@ relay_kernel(MinArgs args) {
     tm.finish();
 }
 
-int relay_block() { return kWave * kRelayW; }
+int relay_block(int shape) { return kWave * (shape == kRelayShape ? 4 : 2); }
 
-const void* relay_kernel_for(int mixed, int pot, int c) {
+const void* relay_kernel_for(int mixed, int pot, int c, int shape) {
     if (mixed || c < 0 || c > 1) return nullptr;
+    if (shape == kRelayPairShape)
+        return c == 0 && pot == kPairLJ ? reinterpret_cast<const void*>(&relay_kernel<1, 2, kPairLJ>)
+                                        : nullptr;
 #define LJ_RELAY(A)                                                                 \
-    (pot == kPairMorse ? reinterpret_cast<const void*>(&relay_kernel<A, kPairMorse>) \
-                       : reinterpret_cast<const void*>(&relay_kernel<A, kPairLJ>))
+    (pot == kPairMorse ? reinterpret_cast<const void*>(&relay_kernel<A, 4, kPairMorse>) \
+                       : reinterpret_cast<const void*>(&relay_kernel<A, 4, kPairLJ>))
     return c == 0 ? LJ_RELAY(1) : LJ_RELAY(2);
 #undef LJ_RELAY
 }

@@ -39,3 +39,22 @@ def test_helper_wavefronts_fp64_bitwise(sizes, pair, m):
     ro = O.minimize(off, x, op)
     for key in KEYS:
         assert np.array_equal(r[key], ro[key], equal_nan=True), key
+
+
+@pytest.mark.parametrize("m", [0, 2, 10])
+def test_two_wavefronts_per_cluster_fp64_bitwise(m):
+    """More clusters than four wavefronts each have SIMDs for: two per cluster,
+    every N of the class among them, and coincident atoms."""
+    sizes = list(range(65)) + [20, 21, 38, 44, 45, 64] * 80
+    off, x = random_starts(sizes, 9150)
+    x = x.copy()
+    o = off[40]
+    x[:, o + 7] = x[:, o + 30]
+    b = lj.ClusterBatch(off)
+    xd = torch.from_numpy(x).cuda()
+    p = lj.lbfgs_params(m=m, max_iter=12 if m == 0 else 60)
+    announce(f"two wavefronts per cluster fp64 m={m} clusters={b.num} max_n={b.max_n}")
+    r = host_dict(lj.minimize(b, xd, p, "fp64"))
+    ro = O.minimize(off, x, oracle_params(p))
+    for key in KEYS:
+        assert np.array_equal(r[key], ro[key], equal_nan=True), key
