@@ -377,22 +377,37 @@ __device__ __forceinline__ double team_max(const double (&vals)[A], TeamScratch<
 // correctly rounded IEEE operation, so the result does not depend on the
 // device.  Used by the Metropolis test (z <= 0) and the Morse pair (z <= rho;
 // the reduction and polynomial hold up to z = 709).
+__device__ __forceinline__ double exp_in_range(double z);
+
 __device__ __forceinline__ double exp_cw(double z) {
     if (!(z >= -708.0)) return 0.0;
+    return exp_in_range(z);
+}
+
+// p r + c with the constant c kept in scalar registers: a literal would be
+// copied to the destination of a multiply-add first, one move per step of the
+// polynomial.
+__device__ __forceinline__ double horner(double p, double r, double c) {
+    asm("" : "+s"(c));
+    return fma(p, r, c);
+}
+
+// exp_cw for z >= -708.
+__device__ __forceinline__ double exp_in_range(double z) {
     const double kf = rint(z * 1.4426950408889634);
     double r = fma(-kf, 6.93147180369123816490e-01, z);
     r = fma(-kf, 1.90821492927058770002e-10, r);
     double p = 1.0 / 6227020800.0;
-    p = fma(p, r, 1.0 / 479001600.0);
-    p = fma(p, r, 1.0 / 39916800.0);
-    p = fma(p, r, 1.0 / 3628800.0);
-    p = fma(p, r, 1.0 / 362880.0);
-    p = fma(p, r, 1.0 / 40320.0);
-    p = fma(p, r, 1.0 / 5040.0);
-    p = fma(p, r, 1.0 / 720.0);
-    p = fma(p, r, 1.0 / 120.0);
-    p = fma(p, r, 1.0 / 24.0);
-    p = fma(p, r, 1.0 / 6.0);
+    p = horner(p, r, 1.0 / 479001600.0);
+    p = horner(p, r, 1.0 / 39916800.0);
+    p = horner(p, r, 1.0 / 3628800.0);
+    p = horner(p, r, 1.0 / 362880.0);
+    p = horner(p, r, 1.0 / 40320.0);
+    p = horner(p, r, 1.0 / 5040.0);
+    p = horner(p, r, 1.0 / 720.0);
+    p = horner(p, r, 1.0 / 120.0);
+    p = horner(p, r, 1.0 / 24.0);
+    p = horner(p, r, 1.0 / 6.0);
     p = fma(p, r, 0.5);
     p = fma(p, r, 1.0);
     p = fma(p, r, 1.0);
@@ -480,34 +495,94 @@ __device__ __forceinline__ void pair_fp32(const float4 p, bool self, float xi, f
 constexpr int kPairLJ = LJ_PAIR_LJ;
 constexpr int kPairMorse = LJ_PAIR_MORSE;
 
+// The FP64 term by the general square root and division, or (IEEE = false) by
+// their operations without the scaling and special-case fix-up that are the
+// identity for the pair distances noted in `range`: sqrt by rsq and the usual
+// refinement, whose half reciprocal root also gives 1 / r for the quotient
+// (the same quotient and root as the general forms on 8.6e9 arguments, among
+// them squares half an ulp off).  An evaluation with a pair outside that range
+// is repeated with the general forms.  The pair loop is bound by issue, and with
+// the polynomial's constants in scalar registers a term takes about 45
+// instructions instead of 70: 1024 x Morse38 FP64 3.7 instead of 4.2 ms, 4096 x
+// Morse60 22 instead of 32 ms, 16384 x Morse13 2.8 instead of 3.6 ms.
+struct MorseRange {
+    uint32_t lo = 0xffffffffu, hi = 0;  // least and greatest high word of r2 (r2 >= 0)
+    __device__ __forceinline__ void note(double r2) {
+        const uint32_t w = (uint32_t)reinterpret_cast<const int2*>(&r2)->y;
+        lo = min(lo, w);
+        hi = max(hi, w);
+    }
+    // r2 >= 2^-600 and below the high word `top`.
+    __device__ __forceinline__ bool holds(uint32_t top) const {
+        return lo >= 0x1a700000u && hi < top;
+    }
+};
+
+// The high word of the r2 at which the exponential falls to e^-400, so that
+// neither the quotient nor its residual is subnormal; 0 (no pair is in range)
+// for a rho that does not keep the numerator within 2^-900 .. 2^900.
+__device__ __forceinline__ uint32_t morse_top(double rho) {
+    const double r = 1.0 + 400.0 / rho, r2 = r * r;
+    return rho >= 1.0e-3 && rho <= 300.0 ? (uint32_t)reinterpret_cast<const int2*>(&r2)->y : 0u;
+}
+
+template <bool IEEE>
+__device__ __forceinline__ double2 morse_term(double r2, bool self, double rho, double c,
+                                              MorseRange& range) {
+    // the self pair: r2 = 1 and then t = 0, both with zero low words already, so
+    // that V and the coefficient are zeros
+    int2 rb = *reinterpret_cast<int2*>(&r2);
+    rb.y = self ? 0x3ff00000 : rb.y;
+    r2 = *reinterpret_cast<double*>(&rb);
+    if constexpr (!IEEE) range.note(r2);
+    double r, y = 0.0;
+    if constexpr (IEEE) {
+        r = sqrt(r2);
+    } else {
+        const double y0 = __builtin_amdgcn_rsq(r2);
+        double h = 0.5 * y0;
+        r = r2 * y0;
+        double d = fma(-h, r, 0.5);
+        r = fma(r, d, r);
+        h = fma(h, d, h);
+        r = fma(fma(-r, r, r2), h, r);
+        r = fma(fma(-r, r, r2), h, r);
+        y = h + h;
+        y = fma(y, fma(-r, y, 1.0), y);
+    }
+    double t = IEEE ? exp_cw(fma(-rho, r, rho)) : exp_in_range(fma(-rho, r, rho));
+    int2 tb = *reinterpret_cast<int2*>(&t);
+    tb.y = self ? 0 : tb.y;
+    t = *reinterpret_cast<double*>(&tb);
+    const double et = t * (t - 2.0);
+    const double fn = (c * t) * (t - 1.0);
+    if constexpr (IEEE) return make_double2(fn / r, et);
+    const double q = fn * y;
+    return make_double2(fma(fma(-r, q, fn), y, q), et);
+}
+
+template <bool IEEE>
 __device__ __forceinline__ void pair_morse64(const double4 p, bool self, double xi, double yi,
-                                             double zi, double rho, double c, double& e,
-                                             double& gx, double& gy, double& gz) {
+                                             double zi, double rho, double c, MorseRange& range,
+                                             double& e, double& gx, double& gy, double& gz) {
     const double dx = xi - p.x;
     const double dy = yi - p.y;
     const double dz = zi - p.z;
     const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-    const double r = sqrt(r2);
-    const double t = self ? 0.0 : exp_cw(fma(-rho, r, rho));
-    e = e + t * (t - 2.0);
-    const double fn = (c * t) * (t - 1.0);
-    const double f = self ? 0.0 : fn / r;
-    gx = fma(f, dx, gx);
-    gy = fma(f, dy, gy);
-    gz = fma(f, dz, gz);
+    const double2 v = morse_term<IEEE>(r2, self, rho, c, range);
+    e = e + v.y;
+    gx = fma(v.x, dx, gx);
+    gy = fma(v.x, dy, gy);
+    gz = fma(v.x, dz, gz);
 }
 
-// The FP64 Morse terms of one distinct pair, with the operations of
-// pair_morse64: .y = V and .x = the gradient coefficient, functions of r2
-// alone.
+// The FP64 Morse terms of one distinct pair: .y = V and .x = the gradient
+// coefficient, functions of r2 alone.
+template <bool IEEE>
 __device__ __forceinline__ double2 term_morse64(double dx, double dy, double dz, double rho,
-                                                double c) {
+                                                double c, MorseRange& range) {
     const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-    const double r = sqrt(r2);
-    const double t = exp_cw(fma(-rho, r, rho));
-    const double et = t * (t - 2.0);
-    const double fn = (c * t) * (t - 1.0);
-    return make_double2(fn / r, et);
+    return morse_term<IEEE>(r2, false, rho, c, range);
 }
 
 // FP32: hardware square root, base-2 exponential and reciprocal.
@@ -581,11 +656,11 @@ __device__ __forceinline__ void pairs_fp64_range(int j0, int j1, int own, int t,
                                                  const double4* __restrict__ pos,
                                                  const double (&x)[3][A], double (&e)[A],
                                                  double (&g)[3][A], double rho, double c,
-                                                 double k24, double km48) {
+                                                 double k24, double km48, MorseRange& range) {
     auto pair = [&](const double4 p, bool self, int a) {
         if constexpr (POT == kPairMorse)
-            pair_morse64(p, self, x[0][a], x[1][a], x[2][a], rho, c, e[a], g[0][a], g[1][a],
-                         g[2][a]);
+            pair_morse64<IEEE>(p, self, x[0][a], x[1][a], x[2][a], rho, c, range, e[a], g[0][a],
+                               g[1][a], g[2][a]);
         else
             pair_fp64<IEEE>(p, self, x[0][a], x[1][a], x[2][a], k24, km48, e[a], g[0][a], g[1][a],
                             g[2][a]);
@@ -634,7 +709,8 @@ __device__ __forceinline__ int used_slots(int n, int w) {
 template <int A, int T, int POT, bool IEEE, bool PACKED = false>
 __device__ __forceinline__ void pairs_fp64(int n, const double4* __restrict__ pos,
                                            const double (&x)[3][A], double (&e)[A],
-                                           double (&g)[3][A], double rho, int w, int t) {
+                                           double (&g)[3][A], double rho, int w, int t,
+                                           MorseRange& range) {
     const double c = -2.0 * rho;
     double k24, km48;
     hold_constants(k24, km48);
@@ -644,7 +720,8 @@ __device__ __forceinline__ void pairs_fp64(int n, const double4* __restrict__ po
         g[0][a] = g[1][a] = g[2][a] = 0.0;
     }
     if constexpr (A * T == kWave) {
-        pairs_fp64_range<A, POT, IEEE, true, PACKED>(0, n, 0, t, pos, x, e, g, rho, c, k24, km48);
+        pairs_fp64_range<A, POT, IEEE, true, PACKED>(0, n, 0, t, pos, x, e, g, rho, c, k24, km48,
+                                                          range);
     } else {
         // slots above the cluster's last atom do no work (a 300-atom cluster in
         // an 8 x 2 team: 5 of 8 wavefronts, one slot each)
@@ -655,10 +732,10 @@ __device__ __forceinline__ void pairs_fp64(int n, const double4* __restrict__ po
                 const int j0 = tile * kWave, j1 = min(n, j0 + kWave);
                 if (tile % W == w)
                     pairs_fp64_range<A, POT, IEEE, true, false, NA>(j0, j1, tile / W, t, pos, x, e,
-                                                                    g, rho, c, k24, km48);
+                                                                    g, rho, c, k24, km48, range);
                 else
                     pairs_fp64_range<A, POT, IEEE, false, false, NA>(j0, j1, 0, t, pos, x, e, g,
-                                                                     rho, c, k24, km48);
+                                                                     rho, c, k24, km48, range);
             }
         };
         const int slots = used_slots<A, T>(n, w);
@@ -714,11 +791,13 @@ __device__ __forceinline__ void up_pair_list(int n, uint2* __restrict__ list, in
 
 constexpr int kUpRounds = 4;
 
+template <bool IEEE>
 __device__ __forceinline__ void pairs_morse64_up(int n, const double4* __restrict__ pos,
                                                  double2* __restrict__ M,
                                                  const uint2* __restrict__ list,
                                                  const double (&x)[3][1], double (&e)[1],
-                                                 double (&g)[3][1], double rho, int t) {
+                                                 double (&g)[3][1], double rho, int t,
+                                                 MorseRange& range) {
     const double c = -2.0 * rho;
     const int P = n * (n - 1) / 2;
     const char* pb = reinterpret_cast<const char*>(pos);
@@ -741,7 +820,8 @@ __device__ __forceinline__ void pairs_morse64_up(int n, const double4* __restric
         }
 #pragma unroll
         for (int u = 0; u < kUpRounds; ++u)
-            tt[u] = term_morse64(pi[u].x - pj[u].x, pi[u].y - pj[u].y, pi[u].z - pj[u].z, rho, c);
+            tt[u] = term_morse64<IEEE>(pi[u].x - pj[u].x, pi[u].y - pj[u].y, pi[u].z - pj[u].z,
+                                       rho, c, range);
 #pragma unroll
         for (int u = 0; u < kUpRounds; ++u)
             if (t + kWave * (r0 + u) < P) {

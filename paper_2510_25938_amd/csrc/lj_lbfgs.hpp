@@ -37,6 +37,7 @@ struct Team {
     int n;
     int li;      // atom index of this thread's slot 0 within the cluster
     double rho;  // Morse range (POT == kPairMorse)
+    uint32_t top;  // morse_top(rho)
     double2* upm;    // up_n x up_n pair matrix
     uint2* uplist;   // up_n (up_n - 1) / 2 pair-list entries
     int up_n;
@@ -229,7 +230,16 @@ struct Team {
             pairs_mixed<A, T, POT>(n, pos32, x, e[0], g, rho,
                                    W == 1 ? 0 : uniform((int)threadIdx.x / kWave), li);
         } else {
-            fp64_pairs<POT == kPairMorse>(x, e[0], g);
+            MorseRange range;
+            fp64_pairs<false>(x, e[0], g, range);
+            if constexpr (POT == kPairMorse) {
+                // a pair outside the range of the short forms: this wavefront
+                // repeats its sums with the general square root and division
+                // (unique pairs: every lane takes some; else the lanes of atoms)
+                const bool takes = (UP && n <= up_n) || active(0);
+                if (__builtin_amdgcn_ballot_w64(takes && !range.holds(top)) != 0)
+                    fp64_pairs<true>(x, e[0], g, range);
+            }
         }
 #pragma unroll
         for (int a = 0; a < A; ++a)
@@ -240,7 +250,8 @@ struct Team {
             // 1/r2 differ from the IEEE quotient, and it makes E not finite:
             // then the evaluation is repeated with the IEEE division
             if (!isfinite(o[0])) {
-                fp64_pairs<true>(x, e[0], g);
+                MorseRange range;
+                fp64_pairs<true>(x, e[0], g, range);
 #pragma unroll
                 for (int a = 0; a < A; ++a)
                     if (!active(a)) e[0][a] = g[0][a] = g[1][a] = g[2][a] = 0.0;
@@ -252,15 +263,15 @@ struct Team {
 
     template <bool IEEE>
     __device__ __forceinline__ void fp64_pairs(const double (&x)[3][A], double (&e)[A],
-                                               double (&g)[3][A]) {
+                                               double (&g)[3][A], MorseRange& range) {
         if constexpr (UP) {
             if (n <= up_n) {
-                pairs_morse64_up(n, pos64, upm, uplist, x, e, g, rho, li);
+                pairs_morse64_up<IEEE>(n, pos64, upm, uplist, x, e, g, rho, li, range);
                 return;
             }
         }
         pairs_fp64<A, T, POT, IEEE, (G > 1)>(
-            n, pos64, x, e, g, rho, W == 1 ? 0 : uniform((int)threadIdx.x / kWave), li);
+            n, pos64, x, e, g, rho, W == 1 ? 0 : uniform((int)threadIdx.x / kWave), li, range);
     }
 
     __device__ __forceinline__ void sum_energy(double (&e)[1][A], double (&o)[1]) {

@@ -60,6 +60,7 @@ __global__ __launch_bounds__(kWave* W) __attribute__((amdgpu_waves_per_eu(OCC)))
     tm.sc = &scratch;
     tm.bank = 0;
     tm.rho = args.rho;
+    tm.top = POT == kPairMorse ? (uint32_t)uniform((int)morse_top(args.rho)) : 0u;
     // kernels at two wavefronts per SIMD whose registers do not hold the history
     // keep half of it in LDS
     constexpr bool kHybrid = HREG && A == 1 && G == 1 && OCC == 2 && (MIXED || W > 1);
@@ -179,6 +180,7 @@ __global__ __launch_bounds__(kWave* W) void energy_grad_kernel(const int32_t* of
     tm.n = n;
     tm.li = threadIdx.x;
     tm.rho = rho;
+    tm.top = POT == kPairMorse ? (uint32_t)uniform((int)morse_top(rho)) : 0u;
     double x[3][A], g[3][A];
 #pragma unroll
     for (int c = 0; c < 3; ++c)

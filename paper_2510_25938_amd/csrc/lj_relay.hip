@@ -77,14 +77,17 @@ template <int A, int POT, bool IEEE>
 __device__ __forceinline__ void relay_first(RelayLds<A>& lds, int j1, int tile, int lane,
                                             const double (&x)[3][1], double rho, double c,
                                             double k24, double km48) {
+    // the Morse pair by its general forms (in the segments' terms too)
+    constexpr bool GEN = IEEE || POT == kPairMorse;
+    MorseRange range;
     double e[1] = {0.0}, g[3][1] = {{0.0}, {0.0}, {0.0}};
     // j1 <= 64: only tile 0 meets its own atoms
     if (tile == 0)
-        pairs_fp64_range<1, POT, IEEE, true, false>(0, j1, 0, lane, lds.pos, x, e, g, rho, c, k24,
-                                                    km48);
+        pairs_fp64_range<1, POT, GEN, true, false>(0, j1, 0, lane, lds.pos, x, e, g, rho, c, k24,
+                                                   km48, range);
     else
-        pairs_fp64_range<1, POT, IEEE, false, false>(0, j1, 0, lane, lds.pos, x, e, g, rho, c, k24,
-                                                     km48);
+        pairs_fp64_range<1, POT, GEN, false, false>(0, j1, 0, lane, lds.pos, x, e, g, rho, c, k24,
+                                                    km48, range);
     lds.acc[tile][0][lane] = make_double2(e[0], g[0][0]);
     lds.acc[tile][1][lane] = make_double2(g[1][0], g[2][0]);
 }
@@ -369,6 +372,7 @@ relay_kernel(MinArgs args) {
     tm.li = lane;
     tm.bank = 0;
     tm.rho = args.rho;
+    tm.top = 0;
     tm.up_n = 0;
     History<1, A, true> H;
     H.init(nullptr, nullptr, args.p.m);
