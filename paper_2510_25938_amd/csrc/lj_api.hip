@@ -214,8 +214,13 @@ int default_class_shape(int c, int max_n, int top_class, int mixed, int pot, int
     // 3.22 instead of 2.80 ms (hence the limit); 8 x LJ98 7.3 instead of
     // 8.9 ms, 384 x LJ98 17.3 instead of 15.4 ms.  Below 20 atoms the hand-overs
     // cost what the shared pairs save (LJ13 3.29 instead of 3.16 us per
-    // iteration, LJ20 3.86 instead of 3.97 us).
-    if (!mixed && c <= 1 && cmax >= 20 && num <= (c == 0 && top_class == 0 ? 2 : 1) * cus)
+    // iteration, LJ20 3.86 instead of 3.97 us), for the Morse pair, whose other
+    // kernel evaluates unique pairs up to 40 atoms, below 24 (8 x Morse20 0.86
+    // instead of 0.80 ms, 8 x Morse24 1.44 instead of 1.53, 8 x Morse38 2.26
+    // instead of 2.81, 512 x Morse38 3.26 instead of 3.53, 256 x Morse98 15.7
+    // instead of 21.1).
+    if (!mixed && c <= 1 && cmax >= (pot == LJ_PAIR_MORSE ? 24 : 20) &&
+        num <= (c == 0 && top_class == 0 ? 2 : 1) * cus)
         return lj::kRelayShape;
     // Two wavefronts per cluster up to one cluster per SIMD (Eq. (1), class 0):
     // 1024, 800 and 600 x LJ38 2.9, 2.6 and 2.6 instead of 3.2, 3.0 and 3.0 ms,
@@ -232,12 +237,12 @@ int default_class_shape(int c, int max_n, int top_class, int mixed, int pot, int
         // (2048 of 4..16 atoms: 0.98 instead of 0.91 ms).  Above 16 atoms in
         // FP64 and beyond two clusters per SIMD alone: the mixed path's packed
         // teams sum 20 atoms and more in another order.  The Morse pair's
-        // one-cluster kernel evaluates unique pairs, the packed ones do not
-        // (2048 x Morse13 FP64: 1.44 packed, 1.45 not, mixed, where only the
-        // polish loses, 1.03 and 1.1; 2048 x Morse30 FP64: 4.7 and 4.3).
+        // one-cluster FP64 kernel evaluates unique pairs, the packed ones do not,
+        // so there the sizes must be closer still (2048 x Morse13 1.13 packed,
+        // 1.38 not, 2048 x Morse30 3.4 and 4.1, but 2048 of 17..32 atoms 3.2
+        // and 2.7).
         const bool many = num > 2 * 4 * cus;
-        const bool alike =
-            (pot == LJ_PAIR_LJ || mixed) && num > 4 * cus && mean > 0.7 * cmax;
+        const bool alike = num > 4 * cus && mean > (pot == LJ_PAIR_LJ || mixed ? 0.7 : 0.9) * cmax;
         int shape = 0;
         if (cmax <= 16)
             shape = many || alike ? 3 : 1;
@@ -249,17 +254,14 @@ int default_class_shape(int c, int max_n, int top_class, int mixed, int pot, int
         // FP64 1.76 instead of 2.27).  The mixed kernel keeps half of its
         // history in LDS then, and wins beside class 1 too (512 chains x 8 of
         // 38..75 atoms: 8.3 instead of 9.0 ms per step; 256 chains level).
-        // Morse pair: not where that ends the unique-pair evaluation (up to 40
-        // atoms, one cluster per wavefront: 2048 x Morse38 FP64 7.4 instead of
-        // 9.1 ms, 3000 of 20..60 atoms 14.4 instead of 16.7, but 4096 x Morse60
-        // 35.8 instead of 32.0; mixed, where only the polish loses, 8192 x
-        // Morse38 13.7 instead of 11.1), nor for the packed mixed kernel, which
-        // spills (16384 x Morse13 2.96 instead of 3.6 ms).
+        // Morse pair, FP64: not where that ends the unique-pair evaluation (up to
+        // 40 atoms, one cluster per wavefront: 2048 x Morse38 6.3 instead of 6.5
+        // to 7.0 ms, 3000 of 20..64 atoms 9.4 instead of 11.1, but 1500 x Morse48
+        // 9.1 instead of 9.7 and 4096 x Morse48 15.6 instead of 17.3).
         const long per_wg = lj::shape_clusters_per_wg(0, shape);
         const long waves = ((long)num + per_wg - 1) / per_wg;
         bool two = waves > 4L * cus && (top_class == 0 || (mixed && top_class == 1 && num > 8 * cus));
-        if (pot == LJ_PAIR_MORSE)
-            two = two && (per_wg > 1 ? !mixed : mean > 40.0 || (mixed && waves > 16L * cus));
+        if (pot == LJ_PAIR_MORSE) two = two && (mixed || per_wg > 1 || mean > 45.0);
         return two ? shape + 4 : shape;
     }
     if (c == 2) return cmax <= 192 ? 1 : 0; // three wavefronts

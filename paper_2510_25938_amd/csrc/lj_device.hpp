@@ -526,7 +526,8 @@ __device__ __forceinline__ uint32_t morse_top(double rho) {
     return rho >= 1.0e-3 && rho <= 300.0 ? (uint32_t)reinterpret_cast<const int2*>(&r2)->y : 0u;
 }
 
-template <bool IEEE>
+// PAD: `self` also stands for a pair to be left out, whose r2 is any.
+template <bool IEEE, bool PAD = false>
 __device__ __forceinline__ double2 morse_term(double r2, bool self, double rho, double c,
                                               MorseRange& range) {
     // the self pair: r2 = 1 and then t = 0, both with zero low words already, so
@@ -553,6 +554,7 @@ __device__ __forceinline__ double2 morse_term(double r2, bool self, double rho, 
     double t = IEEE ? exp_cw(fma(-rho, r, rho)) : exp_in_range(fma(-rho, r, rho));
     int2 tb = *reinterpret_cast<int2*>(&t);
     tb.y = self ? 0 : tb.y;
+    if constexpr (PAD) tb.x = self ? 0 : tb.x;
     t = *reinterpret_cast<double*>(&tb);
     const double et = t * (t - 2.0);
     const double fn = (c * t) * (t - 1.0);
@@ -614,18 +616,17 @@ __device__ __forceinline__ void hold_constants(double& k24, double& km48) {
 }
 
 // One pair's terms: V's part et and the gradient coefficient f, with the
-// operations of pair_fp64 / pair_morse64 (the self pair: exact zeros).
+// operations of pair_fp64 / pair_morse64 (the self pair, and a pair to be left
+// out: exact zeros).
 template <int POT, bool IEEE>
 __device__ __forceinline__ void pair_term64(double dx, double dy, double dz, bool self, double rho,
                                             double c, double k24, double km48, double& f,
-                                            double& et) {
+                                            double& et, MorseRange& range) {
     const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
     if constexpr (POT == kPairMorse) {
-        const double r = sqrt(r2);
-        const double t = self ? 0.0 : exp_cw(fma(-rho, r, rho));
-        et = t * (t - 2.0);
-        const double fn = (c * t) * (t - 1.0);
-        f = self ? 0.0 : fn / r;
+        const double2 v = morse_term<IEEE, true>(r2, self, rho, c, range);
+        f = v.x;
+        et = v.y;
     } else {
         double q = IEEE ? 1.0 / r2 : recip_in_range(r2);
         int2 qb = *reinterpret_cast<int2*>(&q);

@@ -231,15 +231,18 @@ struct Team {
                                    W == 1 ? 0 : uniform((int)threadIdx.x / kWave), li);
         } else {
             MorseRange range;
-            fp64_pairs<false>(x, e[0], g, range);
-            if constexpr (POT == kPairMorse) {
+            bool general = POT == kPairMorse && top == 0;
+            if (!general) {
+                fp64_pairs<false>(x, e[0], g, range);
                 // a pair outside the range of the short forms: this wavefront
                 // repeats its sums with the general square root and division
                 // (unique pairs: every lane takes some; else the lanes of atoms)
-                const bool takes = (UP && n <= up_n) || active(0);
-                if (__builtin_amdgcn_ballot_w64(takes && !range.holds(top)) != 0)
-                    fp64_pairs<true>(x, e[0], g, range);
+                if constexpr (POT == kPairMorse) {
+                    const bool takes = (UP && n <= up_n) || active(0);
+                    general = __builtin_amdgcn_ballot_w64(takes && !range.holds(top)) != 0;
+                }
             }
+            if (POT == kPairMorse && general) fp64_pairs<true>(x, e[0], g, range);
         }
 #pragma unroll
         for (int a = 0; a < A; ++a)

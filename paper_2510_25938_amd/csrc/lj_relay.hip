@@ -14,7 +14,7 @@
 // single-wavefront loop in the same order, so results are bitwise equal.
 //
 // Measured, us per L-BFGS iteration: LJ38 5.1 -> 4.1, LJ64 6.7 -> 4.7, LJ98
-// 12.0 -> 9.9, Morse38 6.9 -> 5.4, Morse98 25.4 -> 17.6 (four wavefronts); 1024 x
+// 12.0 -> 9.9, Morse38 6.0 -> 4.8, Morse98 16.7 -> 12.2 (four wavefronts); 1024 x
 // LJ38 3.2 -> 2.9 ms, 1024 x LJ64 5.7 -> 5.2 ms (two, with one workgroup's
 // wavefronts filling the issue gaps of another's).  The history in LDS
 // instead of the leader's registers cost 0.3-0.6 us per iteration.
@@ -32,11 +32,12 @@ struct RelayLds {
     double4 pos[kWave * A];    // coordinates
     double2 acc[A][2][kWave];  // sums on their way: (e, gx), (gy, gz) per tile and lane
     int cmd, n;
+    int outside[4];  // per tile and segment: a Morse pair outside the short forms' range
 };
 
 // First partner of segment s of S (s = S: n).  Segments grow, so that a
 // wavefront's terms are ready when its predecessor hands over: with t
-// instructions per term (21 for Eq. (1), about 70 for the Morse pair), 4 per
+// instructions per term (21 for Eq. (1), about 50 for the Morse pair), 4 per
 // term for the sums and about 35 for an exchange,
 // n_1 t = n_0 (t + 4) + 35 and n_{s+1} t = n_s (t + 4) + 35.  Two segments of one
 // tile: the second is at most the 20 terms that a helper's registers hold (64
@@ -48,11 +49,11 @@ __device__ __forceinline__ int relay_cut(int s, int n) {
     if (s >= S) return n;
     int v;
     if constexpr (S == 2)
-        v = POT == kPairMorse ? 31 * n - 16
+        v = POT == kPairMorse ? 31 * n - 22
             : A == 1          ? max(29 * n - 48, 64 * (n - 20))
                               : 29 * n - 48;
     else if (POT == kPairMorse)
-        v = s == 1 ? 15 * n - 45 : s == 2 ? 30 * n - 62 : 47 * n - 48;
+        v = s == 1 ? 14 * n - 57 : s == 2 ? 29 * n - 72 : 46 * n - 60;
     else
         v = s == 1 ? 12 * n - 130 : s == 2 ? 26 * n - 190 : 43 * n - 160;
     v >>= 6;
@@ -71,25 +72,31 @@ __device__ __forceinline__ void relay_wait_rest(int seg) {
     for (int s = seg; s < S; ++s) __syncthreads();
 }
 
+// Written by each wavefront in each Morse evaluation, before its last barrier.
+__device__ __forceinline__ void relay_outside(int& out, bool atom, const MorseRange& range,
+                                              uint32_t top) {
+    out = __builtin_amdgcn_ballot_w64(atom && !range.holds(top)) != 0;
+}
+
 // Segment 0 of a tile (the leader's own, and with A = 2 a helper's): partners
 // 0 .. j1 - 1, added directly, and handed on.
 template <int A, int POT, bool IEEE>
 __device__ __forceinline__ void relay_first(RelayLds<A>& lds, int j1, int tile, int lane,
-                                            const double (&x)[3][1], double rho, double c,
-                                            double k24, double km48) {
-    // the Morse pair by its general forms (in the segments' terms too)
-    constexpr bool GEN = IEEE || POT == kPairMorse;
+                                            int n, const double (&x)[3][1], double rho,
+                                            uint32_t top, double c, double k24, double km48) {
     MorseRange range;
     double e[1] = {0.0}, g[3][1] = {{0.0}, {0.0}, {0.0}};
     // j1 <= 64: only tile 0 meets its own atoms
     if (tile == 0)
-        pairs_fp64_range<1, POT, GEN, true, false>(0, j1, 0, lane, lds.pos, x, e, g, rho, c, k24,
+        pairs_fp64_range<1, POT, IEEE, true, false>(0, j1, 0, lane, lds.pos, x, e, g, rho, c, k24,
                                                    km48, range);
     else
-        pairs_fp64_range<1, POT, GEN, false, false>(0, j1, 0, lane, lds.pos, x, e, g, rho, c, k24,
+        pairs_fp64_range<1, POT, IEEE, false, false>(0, j1, 0, lane, lds.pos, x, e, g, rho, c, k24,
                                                     km48, range);
     lds.acc[tile][0][lane] = make_double2(e[0], g[0][0]);
     lds.acc[tile][1][lane] = make_double2(g[1][0], g[2][0]);
+    if constexpr (POT == kPairMorse && !IEEE)
+        relay_outside(lds.outside[tile], tile * kWave + lane < n, range, top);
 }
 
 // Helper of a one-tile cluster (segment seg >= 1): NG groups of 4 terms and
@@ -99,7 +106,7 @@ __device__ __forceinline__ void relay_first(RelayLds<A>& lds, int j1, int tile, 
 // that.
 template <int W, int POT, bool IEEE, int NG>
 __device__ __forceinline__ int relay_helper(RelayLds<1>& lds, int n, int seg, int lane,
-                                            double rho) {
+                                            double rho, uint32_t top) {
     constexpr int S = W;
     constexpr int CAP = kGroup64 * NG;
     const int j0 = relay_cut<S, POT>(seg, n), cnt = relay_cut<S, POT>(seg + 1, n) - j0;
@@ -124,6 +131,7 @@ __device__ __forceinline__ int relay_helper(RelayLds<1>& lds, int n, int seg, in
         const int cmd = uniform(cmd_v);
         if (cmd != (IEEE ? kRelayEvalIeee : kRelayEval)) return cmd;
         const double xi = pi.x, yi = pi.y, zi = pi.z;
+        MorseRange range;
         // past the segment's end the last partner is taken again with a zero
         // term, which leaves every sum as it is
 #pragma unroll
@@ -132,7 +140,7 @@ __device__ __forceinline__ int relay_helper(RelayLds<1>& lds, int n, int seg, in
             dy[u] = yi - dy[u];
             dz[u] = zi - dz[u];
             pair_term64<POT, IEEE>(dx[u], dy[u], dz[u], u == own || u >= cnt, rho, c, k24, km48,
-                                   f[u], et[u]);
+                                   f[u], et[u], range);
             // formed here, before the turn comes (the compiler would sink it)
             asm volatile("" : "+v"(f[u]), "+v"(et[u]));
         }
@@ -150,7 +158,7 @@ __device__ __forceinline__ int relay_helper(RelayLds<1>& lds, int n, int seg, in
             const double4 p = src[k];
             const double ex = xi - p.x, ey = yi - p.y, ez = zi - p.z;
             double ff, ee;
-            pair_term64<POT, IEEE>(ex, ey, ez, k == own, rho, c, k24, km48, ff, ee);
+            pair_term64<POT, IEEE>(ex, ey, ez, k == own, rho, c, k24, km48, ff, ee, range);
             es = es + ee;
             gx = fma(ff, ex, gx);
             gy = fma(ff, ey, gy);
@@ -158,6 +166,8 @@ __device__ __forceinline__ int relay_helper(RelayLds<1>& lds, int n, int seg, in
         }
         lds.acc[0][0][lane] = make_double2(es, gx);
         lds.acc[0][1][lane] = make_double2(gy, gz);
+        if constexpr (POT == kPairMorse && !IEEE)
+            relay_outside(lds.outside[seg], lane < n, range, top);
         relay_wait_rest<S>(seg);
         __syncthreads();  // the next evaluation's first barrier
     }
@@ -170,7 +180,8 @@ constexpr int kRelayTerms = 72;
 
 template <int POT, bool IEEE>
 __device__ __forceinline__ int relay_helper2(RelayLds<2>& lds, double2* __restrict__ terms, int n,
-                                             int tile, int seg, int lane, double rho) {
+                                             int tile, int seg, int lane, double rho,
+                                             uint32_t top) {
     constexpr int S = 2;  // four wavefronts, two tiles
     const int j0 = relay_cut<S, POT, 2>(seg, n), j1 = relay_cut<S, POT, 2>(seg + 1, n);
     const int own = tile * kWave + lane;
@@ -185,12 +196,13 @@ __device__ __forceinline__ int relay_helper2(RelayLds<2>& lds, double2* __restri
         const double xi = pi.x, yi = pi.y, zi = pi.z;
         if (seg == 0) {
             const double x[3][1] = {{xi}, {yi}, {zi}};
-            relay_first<2, POT, IEEE>(lds, j1, tile, lane, x, rho, c, k24, km48);
+            relay_first<2, POT, IEEE>(lds, j1, tile, lane, n, x, rho, top, c, k24, km48);
             relay_wait_rest<S>(0);
             __syncthreads();
             continue;
         }
         double2* t = terms + lane;
+        MorseRange range;
         int j = j0;
         for (; j + kGroup64 <= j1; j += kGroup64, t += kGroup64 * kWave) {
             double4 p[kGroup64];
@@ -200,7 +212,7 @@ __device__ __forceinline__ int relay_helper2(RelayLds<2>& lds, double2* __restri
             for (int u = 0; u < kGroup64; ++u) {
                 double ff, ee;
                 pair_term64<POT, IEEE>(xi - p[u].x, yi - p[u].y, zi - p[u].z, j + u == own, rho, c,
-                                       k24, km48, ff, ee);
+                                       k24, km48, ff, ee, range);
                 t[u * kWave] = make_double2(ff, ee);
             }
         }
@@ -208,7 +220,7 @@ __device__ __forceinline__ int relay_helper2(RelayLds<2>& lds, double2* __restri
             const double4 p = lds.pos[j];
             double ff, ee;
             pair_term64<POT, IEEE>(xi - p.x, yi - p.y, zi - p.z, j == own, rho, c, k24, km48, ff,
-                                   ee);
+                                   ee, range);
             *t = make_double2(ff, ee);
         }
         relay_wait_turn<S>(seg);
@@ -237,6 +249,8 @@ __device__ __forceinline__ int relay_helper2(RelayLds<2>& lds, double2* __restri
         for (; j < j1; ++j, t += kWave) add(lds.pos[j], *t);
         lds.acc[tile][0][lane] = make_double2(es, gx);
         lds.acc[tile][1][lane] = make_double2(gy, gz);
+        if constexpr (POT == kPairMorse && !IEEE)
+            relay_outside(lds.outside[2 + tile], own < n, range, top);
         relay_wait_rest<S>(seg);
         __syncthreads();
     }
@@ -246,7 +260,7 @@ __device__ __forceinline__ int relay_helper2(RelayLds<2>& lds, double2* __restri
 // role / A.
 template <int A, int W, int POT>
 __device__ __forceinline__ void relay_helpers(RelayLds<A>& lds, double2* terms, int role, int lane,
-                                              double rho) {
+                                              double rho, uint32_t top) {
     constexpr int S = W / A;
     const int seg = role / A;
     int n = 0;
@@ -261,23 +275,23 @@ __device__ __forceinline__ void relay_helpers(RelayLds<A>& lds, double2* terms, 
         } else if constexpr (A == 2) {
             double2* own = terms + (role - 2) * kRelayTerms * kWave;  // segment 1: roles 2 and 3
             cmd = cmd == kRelayEval
-                      ? relay_helper2<POT, false>(lds, own, n, role % A, seg, lane, rho)
-                      : relay_helper2<POT, true>(lds, own, n, role % A, seg, lane, rho);
+                      ? relay_helper2<POT, false>(lds, own, n, role % A, seg, lane, rho, top)
+                      : relay_helper2<POT, true>(lds, own, n, role % A, seg, lane, rho, top);
         } else if (cmd == kRelayEvalIeee) {
-            cmd = relay_helper<W, POT, true, 1>(lds, n, seg, lane, rho);
+            cmd = relay_helper<W, POT, true, 1>(lds, n, seg, lane, rho, top);
         } else {
             // the fewest groups that hold the segment
             const int cnt = relay_cut<S, POT>(seg + 1, n) - relay_cut<S, POT>(seg, n);
             if (cnt <= 4)
-                cmd = relay_helper<W, POT, false, 1>(lds, n, seg, lane, rho);
+                cmd = relay_helper<W, POT, false, 1>(lds, n, seg, lane, rho, top);
             else if (cnt <= 8)
-                cmd = relay_helper<W, POT, false, 2>(lds, n, seg, lane, rho);
+                cmd = relay_helper<W, POT, false, 2>(lds, n, seg, lane, rho, top);
             else if (cnt <= 12)
-                cmd = relay_helper<W, POT, false, 3>(lds, n, seg, lane, rho);
+                cmd = relay_helper<W, POT, false, 3>(lds, n, seg, lane, rho, top);
             else if (cnt <= 16)
-                cmd = relay_helper<W, POT, false, 4>(lds, n, seg, lane, rho);
+                cmd = relay_helper<W, POT, false, 4>(lds, n, seg, lane, rho, top);
             else
-                cmd = relay_helper<W, POT, false, 5>(lds, n, seg, lane, rho);
+                cmd = relay_helper<W, POT, false, 5>(lds, n, seg, lane, rho, top);
         }
     }
 }
@@ -312,7 +326,14 @@ struct RelayTeam : Team<1, A, POT> {
             if (i < n) lds->pos[i] = make_double4(x[0][a], x[1][a], x[2][a], 0.0);
         }
         double e[1][A], o[1];
-        share<false>(x, e[0], g);
+        bool general = POT == kPairMorse && this->top == 0;
+        if (!general) {
+            share<false>(x, e[0], g);
+            general = POT == kPairMorse && uniform(lds->outside[0] | lds->outside[1] |
+                                                   lds->outside[2] | lds->outside[3]);
+        }
+        // as in Team::eval: repeated by the general forms
+        if (POT == kPairMorse && general) share<true>(x, e[0], g);
         this->sum_energy(e, o);
         if constexpr (POT == kPairLJ) {
             // as in Team::eval: repeated with the IEEE division if not finite
@@ -334,8 +355,8 @@ struct RelayTeam : Team<1, A, POT> {
         double k24, km48;
         hold_constants(k24, km48);
         const double x0[3][1] = {{x[0][0]}, {x[1][0]}, {x[2][0]}};
-        relay_first<A, POT, IEEE>(*lds, relay_cut<S, POT, A>(1, this->n), 0, lane, x0, this->rho,
-                                  -2.0 * this->rho, k24, km48);
+        relay_first<A, POT, IEEE>(*lds, relay_cut<S, POT, A>(1, this->n), 0, lane, this->n, x0,
+                                  this->rho, this->top, -2.0 * this->rho, k24, km48);
         relay_wait_rest<S>(0);
 #pragma unroll
         for (int a = 0; a < A; ++a) {
@@ -358,13 +379,15 @@ relay_kernel(MinArgs args) {
     __shared__ double2 terms[A == 2 ? 2 * kRelayTerms * kWave : 1];
     const int lane = threadIdx.x % kWave;
     int role = uniform((int)threadIdx.x / kWave);
+    const uint32_t top =
+        POT == kPairMorse ? (uint32_t)uniform((int)morse_top(args.rho)) : 0u;
     // two wavefronts: four workgroups share a CU, and in every other workgroup of
     // an XCD (consecutive workgroups go to the eight XCDs in turn) the second
     // wavefront leads, so that leaders are spread over the SIMDs (1024 x LJ38:
     // 2.88 instead of 2.95 ms)
     if (W == 2) role ^= (int)(blockIdx.x >> 3) & 1;
     if (role != 0) {
-        relay_helpers<A, W, POT>(lds, terms, role, lane, args.rho);
+        relay_helpers<A, W, POT>(lds, terms, role, lane, args.rho, top);
         return;
     }
     RelayTeam<A, W, POT> tm;
@@ -372,7 +395,7 @@ relay_kernel(MinArgs args) {
     tm.li = lane;
     tm.bank = 0;
     tm.rho = args.rho;
-    tm.top = 0;
+    tm.top = top;
     tm.up_n = 0;
     History<1, A, true> H;
     H.init(nullptr, nullptr, args.p.m);

@@ -43,6 +43,8 @@ __device__ __forceinline__ void split_terms(SplitLds& lds, int buf, int k0, int 
                                             const double (&x)[3], double rho, double c,
                                             double k24, double km48, int lane) {
     constexpr int G = 4;
+    constexpr bool GEN = IEEE || POT == kPairMorse;  // the Morse pair by its general forms
+    MorseRange range;
     for (int k = k0; k < k0 + cnt; k += G) {
         double p[3][G];
 #pragma unroll
@@ -53,8 +55,8 @@ __device__ __forceinline__ void split_terms(SplitLds& lds, int buf, int k0, int 
 #pragma unroll
         for (int u = 0; u < G; ++u, self <<= 1) {
             double f, e;
-            pair_term64<POT, IEEE>(x[0] - p[0][u], x[1] - p[1][u], x[2] - p[2][u],
-                                   SELF && in_mask(self), rho, c, k24, km48, f, e);
+            pair_term64<POT, GEN>(x[0] - p[0][u], x[1] - p[1][u], x[2] - p[2][u],
+                                   SELF && in_mask(self), rho, c, k24, km48, f, e, range);
             lds.f[buf][k + u][lane] = f;
             lds.e[buf][k + u][lane] = e;
         }

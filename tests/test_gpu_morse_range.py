@@ -64,3 +64,25 @@ def test_minimisers_at_the_edges(n, shape):
     ro = O.minimize(off, x, op)
     for key in ("xyz", "energy", "gnorm", "iters", "evals", "status"):
         assert np.array_equal(r[key], ro[key], equal_nan=True), key
+
+
+@pytest.mark.parametrize("sizes,prec", [([13] * 1500, "fp64"), ([30] * 1100, "fp64"),
+                                        ([17, 32, 25] * 500, "fp64"), ([24] * 512, "fp64"),
+                                        ([23] * 512, "fp64"), ([45, 46, 48] * 400, "fp64"),
+                                        ([13] * 8200, "mixed"), ([30] * 1100, "mixed")])
+def test_chosen_form_is_the_plain_one(sizes, prec):
+    """The form the built-in rule takes for many Morse clusters, against the
+    one-cluster-per-wavefront form, on all outputs."""
+    off, x = random_starts(sizes, 9900 + len(sizes))
+    b = lj.ClusterBatch(off, pair="morse", rho=6.0)
+    p = lj.lbfgs_params(max_iter=30)
+    xd = torch.from_numpy(x).cuda()
+    announce(f"morse rule {len(sizes)} of up to {max(sizes)} {prec}")
+    r = host_dict(lj.minimize(b, xd, p, prec))
+    try:
+        lj.set_schedule(lj.SCHED_MIN_CLASS[0], prec, max(sizes), 1 if max(sizes) <= 16 else 0)
+        plain = host_dict(lj.minimize(b, xd, p, prec))
+    finally:
+        lj.set_schedule(lj.SCHED_MIN_CLASS[0], prec, max(sizes), -1)
+    for key in ("xyz", "energy", "gnorm", "iters", "evals", "status"):
+        assert np.array_equal(r[key], plain[key], equal_nan=True), key
