@@ -377,41 +377,39 @@ __device__ __forceinline__ double team_max(const double (&vals)[A], TeamScratch<
 // correctly rounded IEEE operation, so the result does not depend on the
 // device.  Used by the Metropolis test (z <= 0) and the Morse pair (z <= rho;
 // the reduction and polynomial hold up to z = 709).
-__device__ __forceinline__ double exp_in_range(double z);
-
-__device__ __forceinline__ double exp_cw(double z) {
-    if (!(z >= -708.0)) return 0.0;
-    return exp_in_range(z);
-}
-
-// p r + c with the constant c kept in scalar registers: a literal would be
-// copied to the destination of a multiply-add first, one move per step of the
-// polynomial.
-__device__ __forceinline__ double horner(double p, double r, double c) {
-    asm("" : "+s"(c));
-    return fma(p, r, c);
-}
+// The coefficients 1 / 12! .. 1 / 3! of the exponential's polynomial.
+constexpr int kExpCoefs = 10;
+struct ExpCoefs {
+    double k[kExpCoefs] = {1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0,
+                           1.0 / 40320.0,     1.0 / 5040.0,     1.0 / 720.0,     1.0 / 120.0,
+                           1.0 / 24.0,        1.0 / 6.0};
+    // Keeps them in scalar registers from here on: a literal would be copied to
+    // the destination of a multiply-add first, one move per step of the
+    // polynomial.  For one evaluation at a time: held through the whole kernel
+    // most of them are spilled and read back.
+    __device__ __forceinline__ void hold() {
+#pragma unroll
+        for (int i = 0; i < kExpCoefs; ++i) asm volatile("" : "+s"(k[i]));
+    }
+};
 
 // exp_cw for z >= -708.
-__device__ __forceinline__ double exp_in_range(double z) {
+__device__ __forceinline__ double exp_in_range(double z, const ExpCoefs& c) {
     const double kf = rint(z * 1.4426950408889634);
     double r = fma(-kf, 6.93147180369123816490e-01, z);
     r = fma(-kf, 1.90821492927058770002e-10, r);
     double p = 1.0 / 6227020800.0;
-    p = horner(p, r, 1.0 / 479001600.0);
-    p = horner(p, r, 1.0 / 39916800.0);
-    p = horner(p, r, 1.0 / 3628800.0);
-    p = horner(p, r, 1.0 / 362880.0);
-    p = horner(p, r, 1.0 / 40320.0);
-    p = horner(p, r, 1.0 / 5040.0);
-    p = horner(p, r, 1.0 / 720.0);
-    p = horner(p, r, 1.0 / 120.0);
-    p = horner(p, r, 1.0 / 24.0);
-    p = horner(p, r, 1.0 / 6.0);
+#pragma unroll
+    for (int i = 0; i < kExpCoefs; ++i) p = fma(p, r, c.k[i]);
     p = fma(p, r, 0.5);
     p = fma(p, r, 1.0);
     p = fma(p, r, 1.0);
     return ldexp(p, (int)kf);
+}
+
+__device__ __forceinline__ double exp_cw(double z, const ExpCoefs& c = ExpCoefs{}) {
+    if (!(z >= -708.0)) return 0.0;
+    return exp_in_range(z, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -506,6 +504,7 @@ constexpr int kPairMorse = LJ_PAIR_MORSE;
 // instructions instead of 70: 1024 x Morse38 FP64 3.7 instead of 4.2 ms, 4096 x
 // Morse60 22 instead of 32 ms, 16384 x Morse13 2.8 instead of 3.6 ms.
 struct MorseRange {
+    ExpCoefs coefs;
     uint32_t lo = 0xffffffffu, hi = 0;  // least and greatest high word of r2 (r2 >= 0)
     __device__ __forceinline__ void note(double r2) {
         const uint32_t w = (uint32_t)reinterpret_cast<const int2*>(&r2)->y;
@@ -551,7 +550,8 @@ __device__ __forceinline__ double2 morse_term(double r2, bool self, double rho, 
         y = h + h;
         y = fma(y, fma(-r, y, 1.0), y);
     }
-    double t = IEEE ? exp_cw(fma(-rho, r, rho)) : exp_in_range(fma(-rho, r, rho));
+    const double z = fma(-rho, r, rho);
+    double t = IEEE ? exp_cw(z, range.coefs) : exp_in_range(z, range.coefs);
     int2 tb = *reinterpret_cast<int2*>(&t);
     tb.y = self ? 0 : tb.y;
     if constexpr (PAD) tb.x = self ? 0 : tb.x;
@@ -805,31 +805,42 @@ __device__ __forceinline__ void pairs_morse64_up(int n, const double4* __restric
     char* mb = reinterpret_cast<char*>(M);
     if (t < n) M[t * n + t] = make_double2(0.0, 0.0);
     // kUpRounds rounds of 64 pairs at a time, so that their LDS reads and
-    // arithmetic overlap; entries past the list repeat its last one and are
-    // not stored
-    const int R = (P + kWave - 1) / kWave;
-    for (int r0 = 0; r0 < R; r0 += kUpRounds) {
-        uint2 w[kUpRounds];
-        double4 pi[kUpRounds], pj[kUpRounds];
-        double2 tt[kUpRounds];
+    // arithmetic overlap, then the rounds that are left together (8 x Morse13, two
+    // rounds, 0.77 instead of 0.83 ms with four); entries past the list repeat
+    // its last one and are not stored
+    auto rounds = [&](int r0, auto count) {
+        constexpr int N = decltype(count)::value;
+        uint2 w[N];
+        double4 pi[N], pj[N];
+        double2 tt[N];
 #pragma unroll
-        for (int u = 0; u < kUpRounds; ++u) w[u] = list[min(t + kWave * (r0 + u), P - 1)];
+        for (int u = 0; u < N; ++u) w[u] = list[min(t + kWave * (r0 + u), P - 1)];
 #pragma unroll
-        for (int u = 0; u < kUpRounds; ++u) {
+        for (int u = 0; u < N; ++u) {
             pi[u] = *reinterpret_cast<const double4*>(pb + (w[u].x & 0xffffu));
             pj[u] = *reinterpret_cast<const double4*>(pb + (w[u].x >> 16));
         }
 #pragma unroll
-        for (int u = 0; u < kUpRounds; ++u)
+        for (int u = 0; u < N; ++u)
             tt[u] = term_morse64<IEEE>(pi[u].x - pj[u].x, pi[u].y - pj[u].y, pi[u].z - pj[u].z,
                                        rho, c, range);
 #pragma unroll
-        for (int u = 0; u < kUpRounds; ++u)
+        for (int u = 0; u < N; ++u)
             if (t + kWave * (r0 + u) < P) {
                 *reinterpret_cast<double2*>(mb + (w[u].y & 0xffffu)) = tt[u];
                 *reinterpret_cast<double2*>(mb + (w[u].y >> 16)) = tt[u];
             }
-    }
+    };
+    static_assert(kUpRounds == 4, "1 to 3 rounds are left");
+    const int R = (P + kWave - 1) / kWave;
+    int r0 = 0;
+    for (; r0 + kUpRounds <= R; r0 += kUpRounds) rounds(r0, SlotCount<kUpRounds>{});
+    if (R - r0 == 3)
+        rounds(r0, SlotCount<3>{});
+    else if (R - r0 == 2)
+        rounds(r0, SlotCount<2>{});
+    else if (R - r0 == 1)
+        rounds(r0, SlotCount<1>{});
     __syncthreads();  // one wavefront: the matrix is complete
     e[0] = 0.0;
     g[0][0] = g[1][0] = g[2][0] = 0.0;

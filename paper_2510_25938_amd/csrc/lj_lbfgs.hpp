@@ -233,6 +233,7 @@ struct Team {
             MorseRange range;
             bool general = POT == kPairMorse && top == 0;
             if (!general) {
+                if constexpr (POT == kPairMorse) range.coefs.hold();
                 fp64_pairs<false>(x, e[0], g, range);
                 // a pair outside the range of the short forms: this wavefront
                 // repeats its sums with the general square root and division
@@ -242,7 +243,11 @@ struct Team {
                     general = __builtin_amdgcn_ballot_w64(takes && !range.holds(top)) != 0;
                 }
             }
-            if (POT == kPairMorse && general) fp64_pairs<true>(x, e[0], g, range);
+            if (POT == kPairMorse && general) {
+                MorseRange any;
+                any.coefs.hold();
+                fp64_pairs<true>(x, e[0], g, any);
+            }
         }
 #pragma unroll
         for (int a = 0; a < A; ++a)

@@ -85,6 +85,7 @@ __device__ __forceinline__ void relay_first(RelayLds<A>& lds, int j1, int tile, 
                                             int n, const double (&x)[3][1], double rho,
                                             uint32_t top, double c, double k24, double km48) {
     MorseRange range;
+    if constexpr (POT == kPairMorse) range.coefs.hold();
     double e[1] = {0.0}, g[3][1] = {{0.0}, {0.0}, {0.0}};
     // j1 <= 64: only tile 0 meets its own atoms
     if (tile == 0)
@@ -132,6 +133,7 @@ __device__ __forceinline__ int relay_helper(RelayLds<1>& lds, int n, int seg, in
         if (cmd != (IEEE ? kRelayEvalIeee : kRelayEval)) return cmd;
         const double xi = pi.x, yi = pi.y, zi = pi.z;
         MorseRange range;
+        if constexpr (POT == kPairMorse) range.coefs.hold();
         // past the segment's end the last partner is taken again with a zero
         // term, which leaves every sum as it is
 #pragma unroll
@@ -203,6 +205,7 @@ __device__ __forceinline__ int relay_helper2(RelayLds<2>& lds, double2* __restri
         }
         double2* t = terms + lane;
         MorseRange range;
+        if constexpr (POT == kPairMorse) range.coefs.hold();
         int j = j0;
         for (; j + kGroup64 <= j1; j += kGroup64, t += kGroup64 * kWave) {
             double4 p[kGroup64];

@@ -45,6 +45,7 @@ __device__ __forceinline__ void split_terms(SplitLds& lds, int buf, int k0, int 
     constexpr int G = 4;
     constexpr bool GEN = IEEE || POT == kPairMorse;  // the Morse pair by its general forms
     MorseRange range;
+    if constexpr (POT == kPairMorse) range.coefs.hold();
     for (int k = k0; k < k0 + cnt; k += G) {
         double p[3][G];
 #pragma unroll
