@@ -215,11 +215,11 @@ int default_class_shape(int c, int max_n, int top_class, int mixed, int pot, int
     // 8.9 ms, 384 x LJ98 17.3 instead of 15.4 ms.  Below 20 atoms the hand-overs
     // cost what the shared pairs save (LJ13 3.29 instead of 3.16 us per
     // iteration, LJ20 3.86 instead of 3.97 us), for the Morse pair, whose other
-    // kernel evaluates unique pairs up to 40 atoms, below 24 (8 x Morse20 0.86
-    // instead of 0.80 ms, 8 x Morse24 1.44 instead of 1.53, 8 x Morse38 2.26
-    // instead of 2.81, 512 x Morse38 3.26 instead of 3.53, 256 x Morse98 15.7
-    // instead of 21.1).
-    if (!mixed && c <= 1 && cmax >= (pot == LJ_PAIR_MORSE ? 24 : 20) &&
+    // kernel evaluates unique pairs up to 40 atoms, below 32 (400 x Morse24 1.67
+    // instead of 1.48 ms, 8 x Morse28 1.31 instead of 1.27, 8 x Morse38 2.33
+    // instead of 2.77, 512 x Morse38 3.32 instead of 3.42, 256 x Morse98 15.3
+    // instead of 20.5).
+    if (!mixed && c <= 1 && cmax >= (pot == LJ_PAIR_MORSE ? 32 : 20) &&
         num <= (c == 0 && top_class == 0 ? 2 : 1) * cus)
         return lj::kRelayShape;
     // Two wavefronts per cluster up to one cluster per SIMD (Eq. (1), class 0):

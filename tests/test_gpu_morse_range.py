@@ -68,7 +68,8 @@ def test_minimisers_at_the_edges(n, shape):
 
 @pytest.mark.parametrize("sizes,prec", [([13] * 1500, "fp64"), ([30] * 1100, "fp64"),
                                         ([17, 32, 25] * 500, "fp64"), ([24] * 512, "fp64"),
-                                        ([23] * 512, "fp64"), ([45, 46, 48] * 400, "fp64"),
+                                        ([32] * 512, "fp64"), ([31] * 512, "fp64"),
+                                        ([45, 46, 48] * 400, "fp64"),
                                         ([13] * 8200, "mixed"), ([30] * 1100, "mixed")])
 def test_chosen_form_is_the_plain_one(sizes, prec):
     """The form the built-in rule takes for many Morse clusters, against the
