@@ -511,9 +511,11 @@ struct MorseRange {
         lo = min(lo, w);
         hi = max(hi, w);
     }
-    // r2 >= 2^-600 and below the high word `top`.
+    // r2 >= 2^-280 and below the high word `top`.  The numerator is at most
+    // 2 rho e^(2 rho) < 2^875 (rho <= 300), so 1 / r <= 2^140 keeps the quotient
+    // finite; an infinite one would make its residual NaN.
     __device__ __forceinline__ bool holds(uint32_t top) const {
-        return lo >= 0x1a700000u && hi < top;
+        return lo >= 0x2e700000u && hi < top;
     }
 };
 
