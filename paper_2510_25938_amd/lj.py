@@ -165,6 +165,16 @@ def _order(stream, *tensors):
             t.record_stream(stream)
 
 
+def _scratch(nbytes, device, stream):
+    """Memory that only work on `stream` uses and the caller never sees: of that
+    stream's own, so that it is handed out again behind that work, also under
+    capture, where nothing is recorded (_order)."""
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
 def precision_code(p):
     if isinstance(p, int):
         return p
@@ -220,8 +230,8 @@ def energy_grad(batch, xyz, precision="fp64", grad=True, stream=None, sigma=1.0,
     if batch.max_n >= SPLIT_EVAL_MIN_ATOMS:  # a few large clusters take scratch memory
         nb = int(lib().lj_energy_grad_workspace_bytes(desc, prec))
         if nb:
-            ws = torch.empty(nb, dtype=torch.uint8, device=xyz.device)
-            _order(stream, xyz, E, g, batch.offset, ws)
+            ws = _scratch(nb, xyz.device, stream)
+            _order(stream, xyz, E, g, batch.offset)
             _check(lib().lj_energy_grad_batch_ws(desc, _ptr(xyz), _ptr(E), _ptr(g), prec, _ptr(ws),
                                                  nb, _stream(stream)))
             return E, g
@@ -255,7 +265,7 @@ def minimize(batch, xyz, params=None, precision="fp64", switch_point=False, work
         nb = minimize_workspace_bytes(batch, params, precision)
         if nb == 0 and batch.num > 0:
             _check(E_ARG)
-        workspace = torch.empty(max(nb, 1), dtype=torch.uint8, device=dev)
+        workspace = _scratch(max(nb, 1), dev, stream)
     _order(stream, x, workspace, batch.offset, *out.values())
     _check(lib().lj_bh_minimize_batch(C.byref(batch.desc(sigma=sigma, epsilon=epsilon)),
                                       _ptr(x), _ptr(out["energy"]),
