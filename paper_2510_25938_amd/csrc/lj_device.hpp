@@ -436,6 +436,15 @@ __device__ __forceinline__ double recip_in_range(double x) {
     return fma(fma(-x, y, 1.0), y, y);
 }
 
+// Orders one wavefront's LDS accesses where no workgroup barrier is needed (they
+// execute in issue order): the fence keeps the compiler from moving a lane's
+// reads of other lanes' words before their stores, the barrier keeps the
+// instructions in place.
+__device__ __forceinline__ void wave_sync() {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_wave_barrier();
+}
+
 // The lanes of the mask as a per-lane condition: the select that uses it reads
 // the scalar mask, so a self test costs one scalar shift per pair instead of a
 // vector compare.

@@ -64,8 +64,7 @@ struct Team {
 
     __device__ __forceinline__ void sync() const {
         if constexpr (G > 1) {
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
         } else {
             __syncthreads();
         }

@@ -93,7 +93,7 @@ __device__ __forceinline__ double split_pass(SplitLds& lds, int n, int tile, int
                 if (lane < 3 * kShare)
                     lds.pos[buf][lane / kShare][kShare * q + lane % kShare] = next;
                 if (it + 1 < chunks) next = fetch(it + 1);
-                __builtin_amdgcn_wave_barrier();
+                wave_sync();
                 const int k0 = kShare * q, cnt = min(kShare, n - it * kChunk - k0);
                 if (it == tile)
                     split_terms<POT, IEEE, true>(lds, buf, k0, cnt, x, rho, c, k24, km48, lane);
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(kUnitWaves* kWave) void split32_kernel(
     if (!tiles) {
         const int j0 = round * kWave, j1 = min(n, j0 + kWave);
         pos[lane] = load(j0 + lane);
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         const float rf = (float)rho, cf = -2.0f * rf;
         const int self = round == tau ? lane : -1;
         float te = 0.0f, tx = 0.0f, ty = 0.0f, tz = 0.0f;
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(kUnitWaves* kWave) void split32_kernel(
         const float4 pj = round == 0 ? pi : load(J * kWave + lane);
         pos[lane] = pj;
         pos[kWave + lane] = pj;
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         float te = 0.0f, tx = 0.0f, ty = 0.0f, tz = 0.0f;
         float3 r;
         int d = lane;  // the partner atom whose reaction this lane ends with
