@@ -135,14 +135,31 @@ __device__ __forceinline__ double split_pass(SplitLds& lds, int n, int tile, int
     return sum;
 }
 
+// The tile of an FP64 workgroup.  The first num nt workgroups (nt: tiles of a
+// cluster of max_n atoms) take the clusters' tiles in order; those from nt on,
+// which only a cluster above max_n has, come last.  Workgroups go to the eight
+// XCDs in turn, so with nt_max (a power of two) of them per cluster in order the
+// empty ones of every cluster fell to the same XCDs: 102 x LJ300, 5 of 8 tiles,
+// 26 us now and 46 so, 93 x LJ700 93 and 132.  The FP32 path's workgroups, many
+// per cluster or short, gain nothing by it.
+struct SplitTile {
+    int b, tile;
+};
+__device__ __forceinline__ SplitTile split_tile(int num, int nt, int nt_max) {
+    const int i = blockIdx.x, first = num * nt, rest = nt_max - nt;
+    return i < first ? SplitTile{i / nt, i % nt}
+                     : SplitTile{(i - first) / rest, nt + (i - first) % rest};
+}
+
 template <int POT>
 __global__ __launch_bounds__(kSplitBlock) void split64_kernel(const int32_t* offset, int64_t total,
                                                               const double* xyz, double* grad,
-                                                              double* partial, int nt_max,
-                                                              double rho, Units u) {
+                                                              double* partial, int num, int nt,
+                                                              int nt_max, double rho, Units u) {
     __shared__ SplitLds lds;
     __shared__ int again;
-    const int b = blockIdx.x / nt_max, tile = blockIdx.x % nt_max;
+    const SplitTile at = split_tile(num, nt, nt_max);
+    const int b = at.b, tile = at.tile;
     const int o = offset[b], n = offset[b + 1] - o;
     if (n <= tile * kWave || n > nt_max * kWave) return;  // (the second: reported as NaN)
     const int lane = threadIdx.x % kWave, wave = uniform((int)threadIdx.x / kWave);
@@ -168,7 +185,7 @@ __global__ __launch_bounds__(kSplitBlock) void split64_kernel(const int32_t* off
             if (wave == 0) es = wave_sum(i < n ? s : 0.0);
         }
     }
-    if (threadIdx.x == 0) partial[blockIdx.x] = es;
+    if (threadIdx.x == 0) partial[b * nt_max + tile] = es;
     if (grad && wave >= 1 && wave <= 3 && i < n) grad[(wave - 1) * total + o + i] = s * u.gscale;
 }
 
@@ -363,29 +380,29 @@ static hipError_t launch_split_t(int mixed, int num, int max_n, const int32_t* o
                                  const double* xyz, double* energy, double* grad, double rho,
                                  Units u, char* ws, hipStream_t st) {
     const EvalShape s = eval_shape(max_n);
-    const int nt = s.W * s.A;
+    const int nt_max = s.W * s.A, nt = (max_n + kWave - 1) / kWave;  // max_n > 256
     double* partial = reinterpret_cast<double*>(ws);
     if (!mixed) {
-        hipLaunchKernelGGL((split64_kernel<POT>), dim3(num * nt), dim3(kSplitBlock), 0, st, off,
-                           total, xyz, grad, partial, nt, rho, u);
+        hipLaunchKernelGGL((split64_kernel<POT>), dim3(num * nt_max), dim3(kSplitBlock), 0, st, off,
+                           total, xyz, grad, partial, num, nt, nt_max, rho, u);
     } else {
-        const int units = split_units(POT, nt);
-        char* p = ws + align256((size_t)num * nt * sizeof(double));
+        const int units = split_units(POT, nt_max);
+        char* p = ws + align256((size_t)num * nt_max * sizeof(double));
         float4* own = reinterpret_cast<float4*>(p);
         float* react =
             reinterpret_cast<float*>(p + align256((size_t)num * units * kWave * sizeof(float4)));
         const int wgs = num * ((units + kUnitWaves - 1) / kUnitWaves);
         hipLaunchKernelGGL((split32_kernel<POT>), dim3(wgs), dim3(kUnitWaves * kWave), 0, st, off,
-                           total, xyz, own, react, nt, units, rho, u);
+                           total, xyz, own, react, nt_max, units, rho, u);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((split32_sum_kernel<POT>), dim3(num * nt), dim3(kWave), 0, st, off,
-                           total, own, react, grad, partial, nt, units, u);
+        hipLaunchKernelGGL((split32_sum_kernel<POT>), dim3(num * nt_max), dim3(kWave), 0, st, off,
+                           total, own, react, grad, partial, nt_max, units, u);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((split_energy_kernel<POT>), dim3(num), dim3(kWave), 0, st, off, partial, nt,
-                       energy, u);
+    hipLaunchKernelGGL((split_energy_kernel<POT>), dim3(num), dim3(kWave), 0, st, off, partial,
+                       nt_max, energy, u);
     return hipGetLastError();
 }
 
