@@ -308,7 +308,11 @@ lj_status lj_bh_step(const lj_batch* chains, const lj_bh_state* state, const lj_
  *   LJ_SCHED_EVAL      lj_energy_grad_batch: W wavefronts per workgroup (1, 2,
  *                      4, 8, 16) x A atom slots per lane (1, 2, 4), keyed by
  *                      precision and max_n rounded up to a power of two;
- *                      64*W*A must be >= max_n.
+ *                      64*W*A must be >= max_n.  lj_energy_grad_batch_ws
+ *                      spreads a call of a few large clusters whatever the
+ *                      entry, except one of LJ_MIXED and Eq. (1) that sums in
+ *                      another order than the built-in shape (16 x 4 for 1025
+ *                      to 2048 atoms): then it runs in the entry's shape.
  *   LJ_SCHED_MIN_LARGE minimiser shape for clusters of 257..1024 atoms, keyed by
  *                      precision: w = 0 (16 wavefronts x 1 atom, the LJ_MIXED
  *                      default), 1 (8 x 2, the LJ_FP64 default) or 2 (4 x 4);
@@ -356,7 +360,9 @@ lj_status lj_get_schedule(int32_t kind, int32_t precision, int32_t max_n, int32_
  * warm-up.  xyz [3][total_atoms] is read only.  Unlike every other call this
  * one SYNCHRONISES the stream (it times launches with HIP events).
  *   ws, ws_bytes     scratch of at least lj_autotune_workspace_bytes().
- *   best_eval_ms     fastest pair-kernel time (nullable).
+ *   best_eval_ms     fastest pair-kernel time (nullable); for a batch that
+ *                    lj_energy_grad_batch_ws spreads over many workgroups, that
+ *                    form is timed too.
  *   best_min_ms      minimisation time with the chosen shapes, -1 if not
  *                    tuned (max_n above LJ_MAX_ATOMS_MIN) (nullable).
  */

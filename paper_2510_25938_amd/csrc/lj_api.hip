@@ -152,13 +152,12 @@ lj::EvalShape eval_schedule(int precision, int max_n) {
 }
 
 // Scratch bytes of the evaluation spread over many workgroups, 0 where one
-// workgroup per cluster is the faster (or the schedule table asks for a shape
-// other than the built-in one).  nt: 64-atom tiles of the largest cluster.
+// workgroup per cluster is the faster.  nt: 64-atom tiles of the largest cluster.
 //   FP64   one workgroup per tile, a round of the chip for every `cus` tiles,
 //          1.7 us per 64 partners and round (Morse pair 2.7), against 4.6, 6.4, 12
 //          and 23 us per 64 partners at nt = 4, 8, 16 and 32 with one workgroup
-//          (Morse 12, 13, 25, 49).  Up to a third more rounds than nt the spread
-//          is the faster at every size: at the limit 102 x LJ300 26 instead of
+//          (Morse 12, 13, 25, 49).  Up to a third as many rounds as nt the
+//          spread is the faster at every size: at the limit 102 x LJ300 26 instead of
 //          34 us, 96 x LJ500 53 and 55, 93 x LJ700 93 and 105, 80 x LJ1000 156
 //          and 191, 85 x LJ1500 355 and 415, 84 x LJ4096 2426 and 2998; Morse 41
 //          and 66, 87 and 107, 151 and 215, 259 and 400, 579 and 884, 4020 and
@@ -169,11 +168,9 @@ lj::EvalShape eval_schedule(int precision, int max_n) {
 //          launches (18 us), against 0.32 nt^2 us: 64 x LJ500 23.0 instead of
 //          27.8 us, 128 28.1 instead of 28.7; 128 x LJ1000 64.9 instead of
 //          90.3 us.  At most 40000 units (70 MB).
-size_t split_eval_ws(const lj_batch* b, int precision, int cus) {
+size_t split_rule_ws(const lj_batch* b, int precision, int cus) {
     const int mixed = precision == LJ_MIXED;
     if (b->max_n <= 256) return 0;
-    const lj::EvalShape s = eval_schedule(precision, b->max_n), d = lj::eval_shape(b->max_n);
-    if (s.W != d.W || s.A != d.A) return 0;
     const long nt = (b->max_n + 63) / 64;
     if (!mixed) {
         const long tiles = std::min((long)b->num * nt, (long)(b->total_atoms / 64) + b->num);
@@ -184,6 +181,25 @@ size_t split_eval_ws(const lj_batch* b, int precision, int cus) {
         if (units > std::min(100 * nt * nt - 4000, 40000L)) return 0;
     }
     return lj::split_eval_bytes(mixed, b->pair, b->num, b->max_n);
+}
+
+// Whether two shapes of clusters above 256 atoms give the same bits: FP64 has one
+// summation order, and the FP32 Morse pair too, while Eq. (1) in FP32 has two
+// (64-atom tiles or the ordered loop).
+bool same_eval_bits(int mixed, int pot, lj::EvalShape s, lj::EvalShape d) {
+    return !mixed || pot == LJ_PAIR_MORSE || lj::use_tiles(s.W, s.A) == lj::use_tiles(d.W, d.A);
+}
+
+// The same for a call.  The schedule table's shape is that of one workgroup per
+// cluster, and its key has no cluster count: an entry tuned on many clusters says
+// nothing of a few, and only one whose sums have another order keeps a call from
+// being spread (one LJ1000: 36 us spread, 189 us by one workgroup).
+size_t split_eval_ws(const lj_batch* b, int precision, int cus) {
+    if (b->max_n <= 256 ||
+        !same_eval_bits(precision == LJ_MIXED, b->pair, eval_schedule(precision, b->max_n),
+                        lj::eval_shape(b->max_n)))
+        return 0;
+    return split_rule_ws(b, precision, cus);
 }
 
 int large_schedule(int precision) {
@@ -1028,6 +1044,11 @@ size_t lj_autotune_workspace_bytes(const lj_batch* batch, int32_t precision) {
     if (check_batch(batch, LJ_MAX_ATOMS_EVAL, "lj_autotune_workspace_bytes") != LJ_OK) return 0;
     size_t off = align_up(sizeof(double) * (size_t)(batch->num > 0 ? batch->num : 1));  // energy
     off = align_up(off + sizeof(double) * 3 * (size_t)batch->total_atoms);              // grad
+    // then the scratch of the spread evaluation, or (later) the minimiser's
+    DeviceInfo di;
+    const size_t spread =
+        batch->num > 0 && device_info(di) == LJ_OK ? split_rule_ws(batch, precision, di.cus) : 0;
+    const size_t eval_end = align_up(off + spread);
     if (batch->max_n <= LJ_MAX_ATOMS_MIN) {
         off = align_up(off + sizeof(double) * 3 * (size_t)batch->total_atoms);  // xyz copy
         off = align_up(off + 5 * sizeof(double) * (size_t)batch->num);          // outputs
@@ -1036,7 +1057,7 @@ size_t lj_autotune_workspace_bytes(const lj_batch* batch, int32_t precision) {
         return 0;
         off = align_up(off + L.total);
     }
-    return off;
+    return std::max(off, eval_end);
 }
 
 lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precision, void* ws,
@@ -1092,16 +1113,18 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
     const int cap = 2 * (pow2_at_least(need_slots) < 64 ? 64 : pow2_at_least(need_slots));
     lj::EvalShape best_shape = lj::eval_shape(batch->max_n);
     float best_ms = 1e30f;
-    const bool spread = split_eval_ws(batch, precision, di.cus) > 0;
+    // a batch that is spread over many workgroups is timed that way too; the table
+    // gets the best shape of one workgroup per cluster all the same, for callers
+    // without scratch memory, unless that shape would end the spread
+    const size_t spread = split_eval_ws(batch, precision, di.cus);
     const int Ws[] = {1, 2, 4, 8, 16}, As[] = {1, 2, 4};
     for (int wi : Ws)
         for (int ai : As) {
             const int slots = 64 * wi * ai;
             if (slots < need_slots || slots > cap) continue;
             lj::EvalShape sh{wi, ai};
-            // a batch spread over many workgroups by the built-in rule keeps
-            // it (and its shape): an entry of another shape would end that
-            if (spread && (wi != best_shape.W || ai != best_shape.A)) continue;
+            if (spread > 0 && !same_eval_bits(mixed, batch->pair, sh, lj::eval_shape(batch->max_n)))
+                continue;
             float ms = 0.f;
             s = time_it([&]() -> lj_status {
                 LJ_HIP_TRY(lj::launch_energy_grad(mixed, batch->pair, sh, batch->num,
@@ -1118,6 +1141,16 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
     if (s == LJ_OK) {
         std::lock_guard<std::mutex> lk(g_sched_mu);
         g_eval_sched[{precision, pow2_at_least(need_slots)}] = best_shape;
+    }
+    if (s == LJ_OK && spread > 0) {
+        float ms = 0.f;
+        s = time_it([&]() -> lj_status {
+            LJ_HIP_TRY(lj::launch_split_eval(mixed, batch->pair, batch->num, batch->max_n,
+                                             batch->offset, batch->total_atoms, xyz, e, g,
+                                             batch->pair_rho, units_of(batch), w + off, st));
+            return LJ_OK;
+        }, ms);
+        if (s == LJ_OK && ms < best_ms) best_ms = ms;
     }
     if (best_eval_ms) *best_eval_ms = best_ms;
     // Minimiser shapes (batches of at most LJ_MAX_ATOMS_MIN atoms): the

@@ -986,8 +986,9 @@ __device__ __forceinline__ void pairs_mixed(int n, const float4* __restrict__ po
 // One wavefront with two atom slots per lane (the 65-128-atom class beside
 // larger ones) keeps the ordered loop: that kernel is at the register limit,
 // and the tiles' staging registers cost more than their saved arithmetic.
+constexpr bool use_tiles(int w, int a) { return w * a * kWave <= 2048 && !(w == 1 && a == 2); }
 template <int W, int A>
-constexpr bool kUseTiles = W * A * kWave <= 2048 && !(W == 1 && A == 2);
+constexpr bool kUseTiles = use_tiles(W, A);
 
 // A tile evaluates 32 ring distances per atom within itself, against n
 // partners per atom in the ordered loop: the tiles win above n = 32 (where a
