@@ -157,17 +157,19 @@ lj::EvalShape eval_schedule(int precision, int max_n) {
 //          1.7 us per 64 partners and round (Morse pair 2.7), against 4.6, 6.4, 12
 //          and 23 us per 64 partners at nt = 4, 8, 16 and 32 with one workgroup
 //          (Morse 12, 13, 25, 49).  Up to a third as many rounds as nt the
-//          spread is the faster at every size: at the limit 102 x LJ300 26 instead of
-//          34 us, 96 x LJ500 53 and 55, 93 x LJ700 93 and 105, 80 x LJ1000 156
-//          and 191, 85 x LJ1500 355 and 415, 84 x LJ4096 2426 and 2998; Morse 41
-//          and 66, 87 and 107, 151 and 215, 259 and 400, 579 and 884, 4020 and
-//          6783; one cluster of 1000 beside 1050 of 13 atoms 160 and 189.  Up to
-//          256 atoms the second launch costs what the split saves (8 x LJ256:
-//          19.0 instead of 18.9 us).
+//          spread is the faster at every size: at the limit 102 x LJ300 26
+//          instead of 34 us, 96 x LJ500 53 and 55, 93 x LJ700 93 and 105, 80 x
+//          LJ1000 156 and 191, 85 x LJ1500 355 and 415, 84 x LJ4096 2426 and
+//          2998; Morse 41 and 66, 87 and 107, 151 and 215, 259 and 400, 579 and
+//          884, 4020 and 6783; one cluster of 1000 beside 1050 of 13 atoms 160
+//          and 189.  Up to 256 atoms the second launch costs what the split saves
+//          (8 x LJ256: 19.0 instead of 18.9 us).
 //   FP32   one wavefront per unit (a pair of tiles), 2.6 ns each and three
 //          launches (18 us), against 0.32 nt^2 us: 64 x LJ500 23.0 instead of
 //          27.8 us, 128 28.1 instead of 28.7; 128 x LJ1000 64.9 instead of
-//          90.3 us.  At most 40000 units (70 MB).
+//          90.3 us.  At most 40000 units; the scratch holds those of a power
+//          of two of tiles per cluster, since a cluster above max_n is evaluated
+//          if it fits the launch shape: at most 169 MB (173 x 1344 atoms).
 size_t split_rule_ws(const lj_batch* b, int precision, int cus) {
     const int mixed = precision == LJ_MIXED;
     if (b->max_n <= 256) return 0;
