@@ -202,6 +202,19 @@ lj_status lj_bh_minimize_batch(const lj_batch* batch, double* xyz, double* energ
                                int32_t precision, void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * lj_minimize_forms - the kernel form that lj_bh_minimize_batch would launch for
+ * each size class of this batch on this stream (a diagnostic; nothing is
+ * enqueued).  forms [4] host, written: for classes up to that of max_n the shape
+ * number of LJ_SCHED_MIN_CLASS0..2 or LJ_SCHED_MIN_LARGE; + 32 for the form of
+ * classes 1 and 2 with two wavefronts per SIMD; 16 or 17 for one cluster per four
+ * or two wavefronts, which only the built-in rule takes (LJ_FP64, calls of few
+ * clusters; on a stream other than the null stream a quarter as many, since
+ * calls on other streams may want those SIMDs); -1 for the classes above.
+ */
+lj_status lj_minimize_forms(const lj_batch* batch, int32_t precision, void* stream,
+                            int32_t* forms);
+
+/*
  * lj_bh_minimize_batch_noalloc - lj_bh_minimize_batch with no workspace
  * argument, for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc).  The

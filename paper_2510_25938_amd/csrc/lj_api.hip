@@ -225,9 +225,25 @@ std::array<int, 4> class_key(int precision, int c, int max_n) {
             pow2_at_least(class_cap(c, max_n) < 1 ? 1 : class_cap(c, max_n))};
 }
 
-// Built-in rule for the shape of class c (0-2); mean: the batch's mean size.
+// How many calls the built-in rule expects beside one another on the device.
+// Helper wavefronts take SIMDs that a call by itself leaves idle but that calls on
+// other streams would fill.  Calls on the null stream run one after another, so
+// one there is taken to have the device; a program that wants its calls to overlap
+// gives them streams of their own, and then the device's four hardware queues may
+// each be running one, so each gets a quarter of the limits.  Measured, ms for 1, 2
+// and 4 calls at once, without / with helper wavefronts: 1024 x LJ38 2.9, 3.8, 5.9 /
+// 2.7, 4.1, 7.1; 512 x LJ38 2.9, 3.6, 4.6 / 2.5, 3.5, 6.4; 256 x LJ98 12.9, 28.9, 18.5 /
+// 10.4, 23.1, 27.1; 512 x Morse38 4.4, 4.4, 5.9 / 3.5, 4.7, 8.6; but 128 x LJ38 2.9
+// (2), 5.7 (4) / 2.2, 4.2; 128 x LJ20 1.28, 1.36 / 1.22, 1.26; 64 x LJ98 11.5, 11.6 /
+// 9.2, 9.4; 128 x Morse32 2.35, 2.74 / 2.31, 2.61; 64 of 20..120 atoms 12.3, 25.2 / 9.9,
+// 18.4.  Basin-hopping steps run on a stream only because the null stream cannot
+// be captured; chains are batched into one call, which is taken to be alone.
+int calls_at_once(hipStream_t st) { return st == nullptr ? 1 : 4; }
+
+// Built-in rule for the shape of class c (0-2); mean: the batch's mean size,
+// calls: calls_at_once.
 int default_class_shape(int c, int max_n, int top_class, int mixed, int pot, int num, double mean,
-                        int cus) {
+                        int cus, int calls) {
     const int cmax = class_cap(c, max_n);
     // Helper wavefronts (FP64) while every cluster's workgroup is resident at
     // once, so that they run on SIMDs which would idle: two workgroups per CU
@@ -242,12 +258,13 @@ int default_class_shape(int c, int max_n, int top_class, int mixed, int pot, int
     // instead of 2.77, 512 x Morse38 3.32 instead of 3.42, 256 x Morse98 15.3
     // instead of 20.5).
     if (!mixed && c <= 1 && cmax >= (pot == LJ_PAIR_MORSE ? 32 : 20) &&
-        num <= (c == 0 && top_class == 0 ? 2 : 1) * cus)
+        num * calls <= (c == 0 && top_class == 0 ? 2 : 1) * cus)
         return lj::kRelayShape;
     // Two wavefronts per cluster up to one cluster per SIMD (Eq. (1), class 0):
     // 1024, 800 and 600 x LJ38 2.9, 2.6 and 2.6 instead of 3.2, 3.0 and 3.0 ms,
     // 1024 x LJ64 5.2 instead of 5.7, 1024 x LJ24 1.60 instead of 1.66.
-    if (!mixed && pot == LJ_PAIR_LJ && c == 0 && top_class == 0 && cmax >= 20 && num <= 4 * cus)
+    if (!mixed && pot == LJ_PAIR_LJ && c == 0 && top_class == 0 && cmax >= 20 &&
+        num * calls <= 4 * cus)
         return lj::kRelayPairShape;
     if (c == 0) {
         // Several clusters per wavefront once the batch has more than one
@@ -314,7 +331,8 @@ bool dense_classes(int num, int max_n, double mean, int cus) {
     return waves > 1.25 * 4 * cus || (mean > 128.0 && max_n <= 256 && num > cus);
 }
 
-int class_schedule(int precision, int c, int max_n, int pot, int num, double mean, int cus) {
+int class_schedule(int precision, int c, int max_n, int pot, int num, double mean, int cus,
+                   int calls) {
     const int top = lj::class_of(max_n < 0 ? 0 : max_n);
     if (c == 3) return large_schedule(precision);
     {
@@ -323,7 +341,7 @@ int class_schedule(int precision, int c, int max_n, int pot, int num, double mea
         if (it != g_class_sched.end() && lj::shape_max_n(c, it->second) >= class_cap(c, max_n))
             return it->second;
     }
-    return default_class_shape(c, max_n, top, precision == LJ_MIXED, pot, num, mean, cus);
+    return default_class_shape(c, max_n, top, precision == LJ_MIXED, pot, num, mean, cus, calls);
 }
 
 // Workspace carve-up of one minimisation call, and the shape of each class.
@@ -334,9 +352,10 @@ struct MinLayout {
     int grid[lj::kNumClasses] = {0, 0, 0, 0};
 };
 
-// force (nullable): a shape per class, -1 for the schedule table's choice.
-lj_status min_layout(int num, int max_n, int64_t total, int mixed, int pot, MinLayout& L,
-                     const int* force = nullptr) {
+// calls: calls_at_once (the sizes do not depend on it).  force (nullable): a shape
+// per class, -1 for the schedule table's choice.
+lj_status min_layout(int num, int max_n, int64_t total, int mixed, int pot, int calls,
+                     MinLayout& L, const int* force = nullptr) {
     DeviceInfo di;
     lj_status s = device_info(di);
     if (s != LJ_OK) return s;
@@ -354,7 +373,7 @@ lj_status min_layout(int num, int max_n, int64_t total, int mixed, int pot, MinL
     for (int c = 0; c <= L.top_class; ++c) {
         L.shape[c] = (force && force[c] >= 0)
                          ? force[c]
-                         : class_schedule(prec, c, max_n, pot, num, mean, di.cus);
+                         : class_schedule(prec, c, max_n, pot, num, mean, di.cus, calls);
         if ((c == 1 || c == 2) && L.shape[c] < lj::class_shapes(c) &&
             dense_classes(num, max_n, mean, di.cus))
             L.shape[c] |= lj::kDenseShape;
@@ -545,9 +564,9 @@ lj_status bh_layout(const lj_batch* ch, const lj_bh_params* bh, int mixed, BhLay
     L.pi = take(sizeof(int32_t) * (size_t)ch->num);
     L.pv = take(sizeof(int32_t) * (size_t)ch->num);
     L.ps = take(sizeof(int32_t) * (size_t)ch->num);
-    lj_status s = min_layout(L.cand_num, ch->max_n, L.cand_total, mixed, ch->pair, L.cand_min);
+    lj_status s = min_layout(L.cand_num, ch->max_n, L.cand_total, mixed, ch->pair, 1, L.cand_min);
     if (s != LJ_OK) return s;
-    s = min_layout(ch->num, ch->max_n, ch->total_atoms, 0, ch->pair, L.polish_min);
+    s = min_layout(ch->num, ch->max_n, ch->total_atoms, 0, ch->pair, 1, L.polish_min);
     if (s != LJ_OK) return s;
     L.min = off;
     const size_t m = L.cand_min.total > L.polish_min.total ? L.cand_min.total : L.polish_min.total;
@@ -806,9 +825,26 @@ size_t lj_minimize_workspace_bytes(const lj_batch* batch, const lj_lbfgs_params*
     (void)params;
     if (check_batch(batch, LJ_MAX_ATOMS_MIN, "lj_minimize_workspace_bytes") != LJ_OK) return 0;
     MinLayout L;
-    if (min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED, batch->pair, L) != LJ_OK)
+    if (min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED, batch->pair,
+                   1, L) != LJ_OK)
         return 0;
     return L.total;
+}
+
+lj_status lj_minimize_forms(const lj_batch* batch, int32_t precision, void* stream,
+                            int32_t* forms) {
+    g_err.clear();
+    lj_status s = check_batch(batch, LJ_MAX_ATOMS_MIN, "lj_minimize_forms");
+    if (s != LJ_OK) return s;
+    if (precision != LJ_FP64 && precision != LJ_MIXED)
+        return fail(LJ_E_ARG, "precision = %d is neither LJ_FP64 nor LJ_MIXED", precision);
+    if (!forms) return fail(LJ_E_ARG, "forms is NULL");
+    MinLayout L;
+    if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED,
+                        batch->pair, calls_at_once(static_cast<hipStream_t>(stream)), L)) != LJ_OK)
+        return s;
+    for (int c = 0; c < lj::kNumClasses; ++c) forms[c] = c <= L.top_class ? L.shape[c] : -1;
+    return LJ_OK;
 }
 
 lj_status lj_bh_minimize_batch(const lj_batch* batch, double* xyz, double* energy, double* gnorm,
@@ -826,7 +862,9 @@ lj_status lj_bh_minimize_batch(const lj_batch* batch, double* xyz, double* energ
         return fail(LJ_E_ARG, "an output array is NULL");
     if (batch->total_atoms > 0 && !xyz) return fail(LJ_E_ARG, "xyz is NULL");
     MinLayout L;
-    if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED, batch->pair, L)) != LJ_OK) return s;
+    if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED,
+                        batch->pair, calls_at_once(static_cast<hipStream_t>(stream)), L)) != LJ_OK)
+        return s;
     if (!ws || ws_bytes < L.total)
         return fail(LJ_E_WORKSPACE, "workspace of %zu bytes given, %zu needed", ws_bytes, L.total);
     return enqueue_minimize(batch, nullptr, xyz, energy, gnorm, iters, evals, status, xyz_switch,
@@ -860,7 +898,9 @@ lj_status lj_bh_minimize_batch_noalloc(const lj_batch* batch, double* xyz, doubl
                     "static scratch holds; use lj_bh_minimize_batch",
                     batch->num, LJ_NOALLOC_MAX_CLUSTERS, LJ_NOALLOC_SCRATCH_BYTES);
     MinLayout L;
-    if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED, batch->pair, L)) != LJ_OK)
+    // calls that overlap would race, so this one has the device
+    if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED,
+                        batch->pair, 1, L)) != LJ_OK)
         return s;
     if (L.total > (size_t)LJ_NOALLOC_SCRATCH_BYTES)
         return fail(LJ_E_WORKSPACE, "lj_bh_minimize_batch_noalloc: %zu bytes of scratch needed, "
@@ -1055,8 +1095,9 @@ size_t lj_autotune_workspace_bytes(const lj_batch* batch, int32_t precision) {
         off = align_up(off + sizeof(double) * 3 * (size_t)batch->total_atoms);  // xyz copy
         off = align_up(off + 5 * sizeof(double) * (size_t)batch->num);          // outputs
         MinLayout L;
-        if (min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED, batch->pair, L) != LJ_OK)
-        return 0;
+        if (min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED,
+                       batch->pair, 1, L) != LJ_OK)
+            return 0;
         off = align_up(off + L.total);
     }
     return std::max(off, eval_end);
@@ -1171,7 +1212,9 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
         int32_t* ev = it + batch->num;
         int32_t* stt = ev + batch->num;
         MinLayout base;
-        if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, mixed, batch->pair, base)) != LJ_OK)
+        const int calls = calls_at_once(st);
+        if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, mixed, batch->pair, calls,
+                            base)) != LJ_OK)
             return s;
         int chosen[lj::kNumClasses] = {-1, -1, -1, -1};
         for (int c = 0; c <= base.top_class; ++c) chosen[c] = base.shape[c] & ~lj::kDenseShape;
@@ -1179,7 +1222,8 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
         lj_lbfgs_defaults(&lp);
         auto time_shapes = [&](const int* force, const lj_lbfgs_params& prm, float& ms) -> lj_status {
             MinLayout L;
-            lj_status r = min_layout(batch->num, batch->max_n, batch->total_atoms, mixed, batch->pair, L, force);
+            lj_status r = min_layout(batch->num, batch->max_n, batch->total_atoms, mixed, batch->pair, calls,
+                                     L, force);
             if (r != LJ_OK) return r;
             return time_it([&]() -> lj_status {
                 LJ_HIP_TRY(hipMemcpyAsync(xc, xyz, sizeof(double) * 3 * (size_t)batch->total_atoms,
@@ -1216,7 +1260,8 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
         int32_t counts[2 * lj::kNumClasses] = {0};
         if (s == LJ_OK) {
             MinLayout L;
-            if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, mixed, batch->pair, L, chosen)) != LJ_OK)
+            if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, mixed, batch->pair,
+                                calls, L, chosen)) != LJ_OK)
                 return s;
             LJ_HIP_TRY(hipMemcpyAsync(counts, w + off + L.cls, sizeof(counts),
                                       hipMemcpyDeviceToHost, st));

@@ -28,7 +28,8 @@ EXPORTED = ["lj_energy_grad_batch", "lj_lbfgs_defaults", "lj_minimize_workspace_
             "lj_bh_minimize_batch", "lj_bh_workspace_bytes", "lj_bh_step", "lj_set_schedule",
             "lj_get_schedule", "lj_autotune_workspace_bytes", "lj_autotune", "lj_status_string",
             "lj_last_error", "lj_abi_version", "lj_bh_minimize_batch_noalloc",
-            "lj_bh_graph_captures", "lj_energy_grad_workspace_bytes", "lj_energy_grad_batch_ws"]
+            "lj_bh_graph_captures", "lj_energy_grad_workspace_bytes", "lj_energy_grad_batch_ws",
+            "lj_minimize_forms"]
 NOALLOC_SCRATCH_BYTES, NOALLOC_MAX_ATOMS, NOALLOC_MAX_CLUSTERS = 1 << 20, 256, 262016
 
 
@@ -111,6 +112,8 @@ def lib():
         L.lj_autotune.argtypes = [C.POINTER(Batch), vp, i32, vp, C.c_size_t, vp,
                                   C.POINTER(C.c_float), C.POINTER(C.c_float)]
         L.lj_autotune.restype = i32
+        L.lj_minimize_forms.argtypes = [C.POINTER(Batch), i32, vp, C.POINTER(i32)]
+        L.lj_minimize_forms.restype = i32
         L.lj_status_string.argtypes = [i32]
         L.lj_status_string.restype = C.c_char_p
         L.lj_last_error.argtypes = []
@@ -244,6 +247,16 @@ def minimize_workspace_bytes(batch, params=None, precision="fp64"):
     params = params or lbfgs_params()
     return int(lib().lj_minimize_workspace_bytes(C.byref(batch.desc()), C.byref(params),
                                                  precision_code(precision)))
+
+
+def minimize_forms(batch, precision="fp64", stream=None):
+    """The kernel form that `minimize` would launch for each size class of the
+    batch on `stream`: a shape number, + 32 for two wavefronts per SIMD, 16 or 17
+    for helper wavefronts, -1 above the largest class."""
+    forms = (C.c_int32 * 4)()
+    _check(lib().lj_minimize_forms(C.byref(batch.desc()), precision_code(precision),
+                                   _stream(stream), forms))
+    return list(forms)
 
 
 def minimize(batch, xyz, params=None, precision="fp64", switch_point=False, workspace=None,
