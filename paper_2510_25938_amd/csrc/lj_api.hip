@@ -246,25 +246,30 @@ int default_class_shape(int c, int max_n, int top_class, int mixed, int pot, int
                         int cus, int calls) {
     const int cmax = class_cap(c, max_n);
     // Helper wavefronts (FP64) while every cluster's workgroup is resident at
-    // once, so that they run on SIMDs which would idle: two workgroups per CU
-    // for class 0 by itself, one for class 1 or beside other classes.  8 x LJ38:
-    // 1.71 instead of 2.14 ms, 512 x LJ38 2.45 instead of 2.82 ms, 640 x LJ38
-    // 3.22 instead of 2.80 ms (hence the limit); 8 x LJ98 7.3 instead of
-    // 8.9 ms, 384 x LJ98 17.3 instead of 15.4 ms.  Below 20 atoms the hand-overs
-    // cost what the shared pairs save (LJ13 3.29 instead of 3.16 us per
-    // iteration, LJ20 3.86 instead of 3.97 us), for the Morse pair, whose other
-    // kernel evaluates unique pairs up to 40 atoms, below 32 (400 x Morse24 1.67
-    // instead of 1.48 ms, 8 x Morse28 1.31 instead of 1.27, 8 x Morse38 2.33
-    // instead of 2.77, 512 x Morse38 3.32 instead of 3.42, 256 x Morse98 15.3
-    // instead of 20.5).
-    if (!mixed && c <= 1 && cmax >= (pot == LJ_PAIR_MORSE ? 32 : 20) &&
-        num * calls <= (c == 0 && top_class == 0 ? 2 : 1) * cus)
+    // once, so that they run on SIMDs which would idle.  Four wavefronts per
+    // cluster: two workgroups per CU for class 0 by itself, one for class 1 or
+    // beside other classes.  8 x LJ38: 1.71 instead of 2.14 ms, 512 x LJ38 2.45
+    // instead of 2.82 ms, 640 x LJ38 3.22 instead of 2.80 ms (hence the limit);
+    // 8 x LJ98 7.3 instead of 8.9 ms, 384 x LJ98 17.3 instead of 15.4 ms.  For the
+    // Morse pair, whose other kernel evaluates unique pairs up to 40 atoms, from 32
+    // atoms on (400 x Morse24 1.67 instead of 1.48 ms, 8 x Morse28 1.31 instead
+    // of 1.27, 8 x Morse38 2.33 instead of 2.77, 512 x Morse38 3.32 instead of 3.42,
+    // 256 x Morse98 15.3 instead of 20.5).
+    // Two wavefronts per cluster (Eq. (1), class 0 by itself) up to one cluster
+    // per SIMD: 1024, 700 and 512 x LJ38 2.63, 2.52 and 2.51 instead of 2.85, 2.80
+    // and 2.79 ms, 1024 x LJ64 5.2 instead of 5.7.
+    // Their one hand-over costs less than three, so below 28 atoms they are the
+    // better for any count, and where most clusters are much smaller below 32
+    // (one / two / four wavefronts: 100 x LJ20 1.24 / 1.11 / 1.21, 512 x LJ24
+    // 1.41 / 1.30 / 1.30, 512 x LJ28 2.26 / 2.15 / 1.97 ms; 511 x LJ13 beside one
+    // LJ20 0.737 / 0.727 / 0.796, one LJ24 0.767 / 0.759 / 0.800, one LJ28 0.864 /
+    // 0.815 / 0.881, one LJ38 1.61 / 1.35 / 1.30 ms; 512 of 8..24 atoms 1.24 / 1.12 /
+    // 1.18).
+    const bool eq1 = pot == LJ_PAIR_LJ, class0_alone = c == 0 && top_class == 0;
+    const int four_from = !eq1 ? 32 : !class0_alone ? 20 : mean >= 20.0 ? 28 : 32;
+    if (!mixed && c <= 1 && cmax >= four_from && num * calls <= (class0_alone ? 2 : 1) * cus)
         return lj::kRelayShape;
-    // Two wavefronts per cluster up to one cluster per SIMD (Eq. (1), class 0):
-    // 1024, 800 and 600 x LJ38 2.9, 2.6 and 2.6 instead of 3.2, 3.0 and 3.0 ms,
-    // 1024 x LJ64 5.2 instead of 5.7, 1024 x LJ24 1.60 instead of 1.66.
-    if (!mixed && pot == LJ_PAIR_LJ && c == 0 && top_class == 0 && cmax >= 20 &&
-        num * calls <= 4 * cus)
+    if (!mixed && eq1 && class0_alone && cmax >= 20 && num * calls <= 4 * cus)
         return lj::kRelayPairShape;
     if (c == 0) {
         // Several clusters per wavefront once the batch has more than one

@@ -6,8 +6,10 @@ import pytest
 import torch
 
 from gpu_util import announce, host_dict
+from oracle import oracle as O
 from paper_2510_25938_amd import lj
 from paper_2510_25938_amd.inputs import random_starts
+from test_gpu_minimize import oracle_params
 
 pytestmark = pytest.mark.gpu
 
@@ -42,6 +44,35 @@ def test_helper_limits():
         mixed = lj.minimize_forms(b, "mixed")
         assert mixed == lj.minimize_forms(b, "mixed", stream=side) and FOUR not in mixed
     assert lj.minimize_forms(batch(98, 8), "fp64")[2:] == [-1, -1]
+
+
+def test_small_and_uneven_clusters_take_two_wavefronts():
+    """Below 28 atoms, and below 32 where most clusters are much smaller, the form
+    with one hand-over is the faster at every count."""
+    def form(sizes):
+        off = np.concatenate([[0], np.cumsum(sizes)])
+        return lj.minimize_forms(lj.ClusterBatch(off), "fp64")[0]
+
+    c = cus()
+    for count in (8, c, 2 * c):
+        assert form([20] * count) == form([27] * count) == TWO
+        assert form([28] * count) == form([13] * (count - 1) + [32]) == FOUR
+        assert form([13] * (count - 1) + [20]) == form([13] * (count - 1) + [31]) == TWO
+        assert form([13] * (count - 1) + [19]) == 0
+
+
+@pytest.mark.parametrize("sizes", [[20] * 5 + [27, 21, 26], [13] * 300 + [31, 2, 0, 1], [24] * 500],
+                         ids=["20to27", "13and31", "24"])
+def test_two_wavefronts_for_small_clusters_bitwise(sizes):
+    off, x = random_starts(sizes, 9995)
+    b = lj.ClusterBatch(off)
+    p = lj.lbfgs_params()
+    announce(f"two wavefronts small clusters={b.num} max_n={b.max_n}")
+    assert lj.minimize_forms(b, "fp64")[0] == TWO
+    r = host_dict(lj.minimize(b, torch.from_numpy(x).cuda(), p, "fp64"))
+    ro = O.minimize(off, x, oracle_params(p))
+    for key in KEYS:
+        assert np.array_equal(r[key], ro[key]), key
 
 
 @pytest.mark.parametrize("n,share,pair", [(38, 1.2, "lj"), (38, 3, "lj"), (98, 0.4, "lj"),
