@@ -1275,10 +1275,19 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
         for (int c = base.top_class < 2 ? base.top_class : 2; c >= 0 && s == LJ_OK; --c) {
             if (counts[lj::kNumClasses + c] == 0) continue;  // no cluster of this class
             const int cap = class_cap(c, batch->max_n);
-            for (int k = 0; k < lj::class_shapes(c) && s == LJ_OK; ++k) {
+            // the numbered shapes, and the built-in rule's form where that has no
+            // number (helper wavefronts): an entry found in the table may have been
+            // tuned on many clusters
+            const int rule = default_class_shape(c, batch->max_n, base.top_class, mixed,
+                                                 batch->pair, batch->num,
+                                                 (double)batch->total_atoms / batch->num, di.cus,
+                                                 calls);
+            for (int q = 0; q <= lj::class_shapes(c) && s == LJ_OK; ++q) {
+                const int k = q < lj::class_shapes(c) ? q : rule;
                 if (k == chosen[c] || lj::shape_max_n(c, k) < cap) continue;
+                if (q == lj::class_shapes(c) && !lj::is_relay(rule)) continue;
                 int force[lj::kNumClasses];
-                for (int q = 0; q < lj::kNumClasses; ++q) force[q] = chosen[q];
+                for (int i = 0; i < lj::kNumClasses; ++i) force[i] = chosen[i];
                 force[c] = k;
                 float ms = 0.f;
                 s = time_shapes(force, lp, ms);
@@ -1288,8 +1297,8 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
                 }
             }
             if (s == LJ_OK) {
-                // the form with helper wavefronts has no number in the table:
-                // where it stays fastest, the built-in rule stays in charge
+                // where a form with helper wavefronts is fastest, no entry: the
+                // built-in rule takes it
                 std::lock_guard<std::mutex> lk(g_sched_mu);
                 if (lj::is_relay(chosen[c]))
                     g_class_sched.erase(class_key(precision, c, batch->max_n));

@@ -369,19 +369,45 @@ def autotune(batch, xyz, precision="mixed", stream=None, cache=None):
         if os.path.exists(cache):
             with open(cache) as fh:
                 table = json.load(fh)
-        key = "fp64" if prec == FP64 else "mixed"
-        p2 = 1
-        while p2 < max(batch.max_n, 1):
-            p2 *= 2
-        table.setdefault(key, {}).setdefault("eval", {})[str(p2)] = [w, a]
-        if res["min_large"] is not None:
-            table[key]["min_large"] = res["min_large"]
-        if res["min_class"]:
-            table[key].setdefault("min_class", {})[str(batch.max_n)] = {
-                str(c): k for c, k in res["min_class"].items()}
+        _merge_schedules(table.setdefault("fp64" if prec == FP64 else "mixed", {}), batch, res)
         with open(cache, "w") as fh:
             json.dump(table, fh, indent=1, sort_keys=True)
     return res
+
+
+def _pow2_at_least(n):
+    p2 = 1
+    while p2 < n:
+        p2 *= 2
+    return p2
+
+
+def _class_key(c, max_n):
+    """The part of the library's schedule key of class c that max_n decides."""
+    return _class_of(max_n), _pow2_at_least(max(min(max_n, (64, 128, 256)[c]), 1))
+
+
+def _merge_schedules(entry, batch, res):
+    """Puts autotune's result into a cache's entry for one precision.  The classes
+    that the batch holds replace every record of the same table key: one without
+    a shape in `res` is back on the built-in rule, and an older record would bring
+    its shape back."""
+    entry.setdefault("eval", {})[str(_pow2_at_least(max(batch.max_n, 1)))] = list(res["eval"][:2])
+    if res["min_large"] is not None:
+        entry["min_large"] = res["min_large"]
+    if res["min_ms"] is None:
+        return
+    held = {_class_of(int(n)) for n in set(batch.sizes)}
+    records = entry.setdefault("min_class", {})
+    for n in list(records):
+        for c in held & {0, 1, 2}:
+            if _class_key(c, int(n)) == _class_key(c, batch.max_n):
+                records[n].pop(str(c), None)
+        if not records[n]:
+            del records[n]
+    if res["min_class"]:
+        records.setdefault(str(batch.max_n), {}).update(
+            {str(c): k for c, k in res["min_class"].items()})
 
 
 def load_schedules(cache):
