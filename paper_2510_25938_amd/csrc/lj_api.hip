@@ -1286,6 +1286,10 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
                 const int k = q < lj::class_shapes(c) ? q : rule;
                 if (k == chosen[c] || lj::shape_max_n(c, k) < cap) continue;
                 if (q == lj::class_shapes(c) && !lj::is_relay(rule)) continue;
+                // class 1, FP64: both shapes are one kernel
+                if (lj::minimize_kernel_for(mixed, batch->pair, c, k) ==
+                    lj::minimize_kernel_for(mixed, batch->pair, c, chosen[c]))
+                    continue;
                 int force[lj::kNumClasses];
                 for (int i = 0; i < lj::kNumClasses; ++i) force[i] = chosen[i];
                 force[c] = k;
