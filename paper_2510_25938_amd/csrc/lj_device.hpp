@@ -983,9 +983,8 @@ __device__ __forceinline__ void pairs_mixed(int n, const float4* __restrict__ po
 // ordered-pair convention of pairs_mixed (E = 2 sum e_i): a unique pair adds
 // twice its term to the lane that evaluates it.
 // ---------------------------------------------------------------------------
-// One wavefront with two atom slots per lane (the 65-128-atom class beside
-// larger ones) keeps the ordered loop: that kernel is at the register limit,
-// and the tiles' staging registers cost more than their saved arithmetic.
+// The evaluation's shape of one wavefront with two atom slots per lane keeps the
+// ordered loop, an order of the FP32 sums that callers of that shape have had.
 constexpr bool use_tiles(int w, int a) { return w * a * kWave <= 2048 && !(w == 1 && a == 2); }
 template <int W, int A>
 constexpr bool kUseTiles = use_tiles(W, A);

@@ -109,8 +109,6 @@ const void* relay_kernel_for(int mixed, int pot, int c, int shape);
 int relay_block(int shape);
 // Added to a shape of class 1 or 2: its form for two wavefronts per SIMD.
 constexpr int kDenseShape = 32;
-const void* relay_kernel_for(int mixed, int pot, int c, int shape);  // nullptr: none
-int relay_block(int shape);
 const void* minimize_kernel_for(int mixed, int pot, int c, int shape);
 hipError_t launch_plan(const int32_t* offset, int num, int max_n, const int32_t* active, Plan plan,
                        int32_t* status, hipStream_t st);
