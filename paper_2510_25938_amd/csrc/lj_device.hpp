@@ -426,7 +426,7 @@ __device__ __forceinline__ double exp_cw(double z, const ExpCoefs& c = ExpCoefs{
 // own rounding, and the correction y + y (1 - x y) (an exact residual) then
 // rounds to the quotient.  One instruction fewer than two Newton steps; equal
 // to 1.0 / x on 1.7e10 arguments, among them mantissas next to 1 and 2 and
-// reciprocals next to rounding midpoints.  For smaller x the pair term
+// reciprocals next to rounding midpoints (the tests repeat 3e5 pair distances).  For smaller x the pair term
 // s6 = q^3 overflows in both forms (the energy is not finite) and for larger x
 // both give s6 = 0; a non-finite energy is recomputed with the IEEE division.
 __device__ __forceinline__ double recip_in_range(double x) {
@@ -506,8 +506,8 @@ constexpr int kPairMorse = LJ_PAIR_MORSE;
 // their operations without the scaling and special-case fix-up that are the
 // identity for the pair distances noted in `range`: sqrt by rsq and the usual
 // refinement, whose half reciprocal root also gives 1 / r for the quotient
-// (the same quotient and root as the general forms on 8.6e9 arguments, among
-// them squares half an ulp off).  An evaluation with a pair outside that range
+// (the same quotient and root as the general forms on 8.6e9 arguments in the
+// range, among them squares half an ulp off; the tests repeat 9e5 pair distances).  An evaluation with a pair outside that range
 // is repeated with the general forms.  The pair loop is bound by issue, and with
 // the polynomial's constants in scalar registers a term takes about 45
 // instructions instead of 70: 1024 x Morse38 FP64 3.7 instead of 4.2 ms, 4096 x

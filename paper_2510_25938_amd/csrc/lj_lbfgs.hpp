@@ -408,8 +408,9 @@ struct History<W, A, true> {
 // hands the oldest of them to a ring in LDS, where an atom's pair is a 48-byte
 // record (three 16-byte reads per lane, which touch every bank once per eight
 // lanes), read ahead of the reductions.  With it the mixed kernels of 1, 2 and 3
-// wavefronts fit 256 registers with at most 28 bytes of scratch (302, 408 and 410
-// registers with the whole history in registers).
+// wavefronts fit 256 registers with at most 28 bytes of scratch for Eq. (1) and 48
+// for the Morse pair (304, 410 and 410 registers, Morse 322 and 396, with the
+// whole history in registers; four wavefronts: 56 and 88 bytes of scratch).
 template <int W, int KR>
 struct HistoryHybrid {
     static constexpr int T = kWave * W;

@@ -271,9 +271,10 @@ hipError_t launch_energy_grad(int mixed, int pot, EvalShape s, int num, const in
 //                           (N <= 16)
 //                        2  two clusters per wavefront, 32 lanes each (N <= 32)
 //                        3  four clusters per wavefront, 16 lanes each (N <= 16)
-//                        4-7  shapes 0-3 compiled for two wavefronts per SIMD
-//                           (at most 256 registers, the rest spilled): for
-//                           batches of more wavefronts than SIMDs
+//                        4-7  shapes 0-3 compiled for two wavefronts per SIMD (at
+//                           most 256 registers; mixed 4 and 5 keep half of the
+//                           history in LDS, mixed 6 and 7 spill 39 registers,
+//                           Morse 63): for batches of more wavefronts than SIMDs
 //   class 1 (N <= 128):  0  two wavefronts;  1  the same with FP32 pairs summed
 //                           in the ordered loop
 //   class 2 (N <= 256):  0  four wavefronts;  1  three wavefronts (N <= 192)

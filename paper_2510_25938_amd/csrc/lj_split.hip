@@ -43,7 +43,9 @@ __device__ __forceinline__ void split_terms(SplitLds& lds, int buf, int k0, int 
                                             const double (&x)[3], double rho, double c,
                                             double k24, double km48, int lane) {
     constexpr int G = 4;
-    constexpr bool GEN = IEEE || POT == kPairMorse;  // the Morse pair by its general forms
+    // the Morse pair by its general forms: the short ones (about 45 instead of 70
+    // instructions) would need the repeat that Eq. (1) has; not tried here
+    constexpr bool GEN = IEEE || POT == kPairMorse;
     MorseRange range;
     if constexpr (POT == kPairMorse) range.coefs.hold();
     for (int k = k0; k < k0 + cnt; k += G) {
