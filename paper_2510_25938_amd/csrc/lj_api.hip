@@ -225,20 +225,54 @@ std::array<int, 4> class_key(int precision, int c, int max_n) {
             pow2_at_least(class_cap(c, max_n) < 1 ? 1 : class_cap(c, max_n))};
 }
 
-// How many calls the built-in rule expects beside one another on the device.
-// Helper wavefronts take SIMDs that a call by itself leaves idle but that calls on
-// other streams would fill.  Calls on the null stream run one after another, so
-// one there is taken to have the device; a program that wants its calls to overlap
-// gives them streams of their own, and then the device's four hardware queues may
-// each be running one, so each gets a quarter of the limits.  Measured, ms for 1, 2
-// and 4 calls at once, without / with helper wavefronts: 1024 x LJ38 2.9, 3.8, 5.9 /
-// 2.7, 4.1, 7.1; 512 x LJ38 2.9, 3.6, 4.6 / 2.5, 3.5, 6.4; 256 x LJ98 12.9, 28.9, 18.5 /
-// 10.4, 23.1, 27.1; 512 x Morse38 4.4, 4.4, 5.9 / 3.5, 4.7, 8.6; but 128 x LJ38 2.9
-// (2), 5.7 (4) / 2.2, 4.2; 128 x LJ20 1.28, 1.36 / 1.22, 1.26; 64 x LJ98 11.5, 11.6 /
-// 9.2, 9.4; 128 x Morse32 2.35, 2.74 / 2.31, 2.61; 64 of 20..120 atoms 12.3, 25.2 / 9.9,
-// 18.4.  Basin-hopping steps run on a stream only because the null stream cannot
-// be captured; chains are batched into one call, which is taken to be alone.
-int calls_at_once(hipStream_t st) { return st == nullptr ? 1 : 4; }
+// The calls that the built-in rule expects beside one another on the device: the
+// caller streams that made two or more of the last eight larger calls (or four,
+// the device's hardware queues, where four or more streams made them).  One call
+// on another stream, as a minimisation ahead of basin-hopping steps, does not
+// count.  Helper wavefronts take SIMDs that a call by itself leaves idle
+// but that calls on other streams would fill, so their limits are divided by
+// that number; calls of up to a quarter of the CUs fit beside three like them and
+// are not counted.  Only a choice among forms with the same results depends on it.
+// Measured, ms for 1, 2 and 4 calls at once, without / with helper wavefronts: 1024 x
+// LJ38 2.9, 3.8, 5.9 / 2.7, 4.1, 7.1; 512 x LJ38 2.9, 3.6, 4.6 / 2.5, 3.5, 6.4; 256 x
+// LJ98 12.9, 28.9, 18.5 / 10.4, 23.1, 27.1; 512 x Morse38 4.4, 4.4, 5.9 / 3.5, 4.7,
+// 8.6; but at a quarter of the limits 128 x LJ38 2.9 (2), 5.7 (4) / 2.2, 4.2; 128 x
+// LJ20 1.28, 1.36 / 1.22, 1.26; 64 x LJ98 11.5, 11.6 / 9.2, 9.4; 128 x Morse32 2.35,
+// 2.74 / 2.31, 2.61; 64 of 20..120 atoms 12.3, 25.2 / 9.9, 18.4.  Asking events whether
+// other calls are still in flight instead let the first calls of every burst
+// take the chip (4 x 256 x LJ98 22.0 ms).
+constexpr int kRecentCalls = 8;
+struct RecentCalls {
+    hipStream_t stream[kRecentCalls];
+    int count = 0, at = 0;
+};
+std::mutex g_recent_mu;
+std::vector<RecentCalls> g_recent;  // per device
+
+// note: the call of num clusters is about to be enqueued on st.  A call under
+// capture says nothing of when it will run: it is taken to be alone.
+int calls_at_once(hipStream_t st, int64_t num, int cus, bool note) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 1;
+    if (st && (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone))
+        return 1;
+    std::lock_guard<std::mutex> lk(g_recent_mu);
+    if ((int)g_recent.size() <= dev) g_recent.resize(dev + 1);
+    RecentCalls& r = g_recent[dev];
+    if (note && 4 * num > cus) {
+        r.stream[r.at] = st;
+        r.at = (r.at + 1) % kRecentCalls;
+        r.count = std::min(r.count + 1, kRecentCalls);
+    }
+    std::map<hipStream_t, int> made;
+    made[st] += 2;
+    for (int k = 0; k < r.count; ++k) ++made[r.stream[k]];
+    if (made.size() >= 4) return 4;
+    int calls = 0;
+    for (const auto& m : made) calls += m.second >= 2;
+    return calls;
+}
 
 // Built-in rule for the shape of class c (0-2); mean: the batch's mean size,
 // calls: calls_at_once.
@@ -545,7 +579,7 @@ struct BhLayout {
     int cand_num = 0;
 };
 
-lj_status bh_layout(const lj_batch* ch, const lj_bh_params* bh, int mixed, BhLayout& L) {
+lj_status bh_layout(const lj_batch* ch, const lj_bh_params* bh, int mixed, int calls, BhLayout& L) {
     const int n = bh->cands;
     L.cand_num = ch->num * n;
     L.cand_total = ch->total_atoms * n;
@@ -569,9 +603,10 @@ lj_status bh_layout(const lj_batch* ch, const lj_bh_params* bh, int mixed, BhLay
     L.pi = take(sizeof(int32_t) * (size_t)ch->num);
     L.pv = take(sizeof(int32_t) * (size_t)ch->num);
     L.ps = take(sizeof(int32_t) * (size_t)ch->num);
-    lj_status s = min_layout(L.cand_num, ch->max_n, L.cand_total, mixed, ch->pair, 1, L.cand_min);
+    lj_status s = min_layout(L.cand_num, ch->max_n, L.cand_total, mixed, ch->pair, calls,
+                             L.cand_min);
     if (s != LJ_OK) return s;
-    s = min_layout(ch->num, ch->max_n, ch->total_atoms, 0, ch->pair, 1, L.polish_min);
+    s = min_layout(ch->num, ch->max_n, ch->total_atoms, 0, ch->pair, calls, L.polish_min);
     if (s != LJ_OK) return s;
     L.min = off;
     const size_t m = L.cand_min.total > L.polish_min.total ? L.cand_min.total : L.polish_min.total;
@@ -844,9 +879,12 @@ lj_status lj_minimize_forms(const lj_batch* batch, int32_t precision, void* stre
     if (precision != LJ_FP64 && precision != LJ_MIXED)
         return fail(LJ_E_ARG, "precision = %d is neither LJ_FP64 nor LJ_MIXED", precision);
     if (!forms) return fail(LJ_E_ARG, "forms is NULL");
+    DeviceInfo di;
+    if ((s = device_info(di)) != LJ_OK) return s;
+    const int calls = calls_at_once(static_cast<hipStream_t>(stream), batch->num, di.cus, false);
     MinLayout L;
     if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED,
-                        batch->pair, calls_at_once(static_cast<hipStream_t>(stream)), L)) != LJ_OK)
+                        batch->pair, calls, L)) != LJ_OK)
         return s;
     for (int c = 0; c < lj::kNumClasses; ++c) forms[c] = c <= L.top_class ? L.shape[c] : -1;
     return LJ_OK;
@@ -866,9 +904,12 @@ lj_status lj_bh_minimize_batch(const lj_batch* batch, double* xyz, double* energ
     if (!energy || !gnorm || !iters || !evals || !status)
         return fail(LJ_E_ARG, "an output array is NULL");
     if (batch->total_atoms > 0 && !xyz) return fail(LJ_E_ARG, "xyz is NULL");
+    DeviceInfo di;
+    if ((s = device_info(di)) != LJ_OK) return s;
+    const int calls = calls_at_once(static_cast<hipStream_t>(stream), batch->num, di.cus, true);
     MinLayout L;
     if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, precision == LJ_MIXED,
-                        batch->pair, calls_at_once(static_cast<hipStream_t>(stream)), L)) != LJ_OK)
+                        batch->pair, calls, L)) != LJ_OK)
         return s;
     if (!ws || ws_bytes < L.total)
         return fail(LJ_E_WORKSPACE, "workspace of %zu bytes given, %zu needed", ws_bytes, L.total);
@@ -926,7 +967,7 @@ size_t lj_bh_workspace_bytes(const lj_batch* chains, const lj_bh_params* bh,
     if (check_batch(chains, LJ_MAX_ATOMS_MIN, "lj_bh_workspace_bytes") != LJ_OK) return 0;
     if (check_bh(chains, bh) != LJ_OK) return 0;
     BhLayout L;
-    if (bh_layout(chains, bh, precision == LJ_MIXED, L) != LJ_OK) return 0;
+    if (bh_layout(chains, bh, precision == LJ_MIXED, 1, L) != LJ_OK) return 0;
     return L.total;
 }
 
@@ -949,7 +990,11 @@ lj_status lj_bh_step(const lj_batch* chains, const lj_bh_state* state, const lj_
     if (trace && trace->capacity_steps < 0) return fail(LJ_E_ARG, "trace capacity < 0");
     const int mixed = precision == LJ_MIXED;
     BhLayout L;
-    if ((s = bh_layout(chains, bh, mixed, L)) != LJ_OK) return s;
+    DeviceInfo di;
+    if ((s = device_info(di)) != LJ_OK) return s;
+    const int calls = calls_at_once(static_cast<hipStream_t>(stream),
+                                    (int64_t)chains->num * bh->cands, di.cus, true);
+    if ((s = bh_layout(chains, bh, mixed, calls, L)) != LJ_OK) return s;
     if (!ws || ws_bytes < L.total)
         return fail(LJ_E_WORKSPACE, "workspace of %zu bytes given, %zu needed", ws_bytes, L.total);
 
@@ -1217,7 +1262,7 @@ lj_status lj_autotune(const lj_batch* batch, const double* xyz, int32_t precisio
         int32_t* ev = it + batch->num;
         int32_t* stt = ev + batch->num;
         MinLayout base;
-        const int calls = calls_at_once(st);
+        const int calls = calls_at_once(st, batch->num, di.cus, false);
         if ((s = min_layout(batch->num, batch->max_n, batch->total_atoms, mixed, batch->pair, calls,
                             base)) != LJ_OK)
             return s;

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import announce, host_dict, to_dev
+from gpu_util import announce, host_dict, settle, to_dev
 from paper_2510_25938_amd import lj
 from paper_2510_25938_amd.inputs import random_starts
 
@@ -25,6 +25,7 @@ def test_tuning_few_clusters_brings_the_rule_back(tmp_path, n, cls, count):
     cache = tmp_path / "sched.json"
     cache.write_text(json.dumps({"fp64": {"min_class": {str(n): {str(cls): 0}}}}))
     announce(f"autotune helpers {count} x LJ{n}")
+    settle(None)
     rule = lj.minimize_forms(b, "fp64")[cls]
     assert rule in (16, 17)
     want = host_dict(lj.minimize(b, xd, p, "fp64"))

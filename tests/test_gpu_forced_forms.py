@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import test_gpu_dense
-from gpu_util import announce, host, host_dict, to_dev
+from gpu_util import announce, host, host_dict, settle, to_dev
 from oracle import oracle as O
 from paper_2510_25938_amd import lj
 from paper_2510_25938_amd.inputs import random_starts
@@ -58,6 +58,7 @@ def test_class1_forms_on_both_sides_of_a_limit(count, below, above):
     sizes = [65 + (k * 37) % 64 for k in range(count)] + [65]
     off, x = random_starts(sizes, 9710)
     p = lj.lbfgs_params(max_iter=40)
+    settle(None)
     out = []
     for k, form in ((count, below), (count + 1, above)):
         b, xd = to_dev(off[:k + 1], np.ascontiguousarray(x[:, :off[k]]))
@@ -89,6 +90,7 @@ def test_batches_of_the_other_files_reach_their_forms():
         off = np.concatenate([[0], np.cumsum(sizes)])
         return lj.minimize_forms(lj.ClusterBatch(off, pair=pair), precision)
 
+    settle(None)
     for precision in ("fp64", "mixed"):  # half of the history in LDS
         assert forms(test_gpu_dense.TWO_WAVES, precision)[1] & DENSE
         assert forms(test_gpu_dense.THREE_WAVES, precision)[2] == DENSE + 1

@@ -1,11 +1,11 @@
-"""The kernel forms that the built-in rule takes: helper wavefronts up to the
-limits of a call that has the device on the null stream, up to a quarter of them
-on a stream of the caller's, and the same results either way."""
+"""The kernel forms that the built-in rule takes: helper wavefronts up to limits
+that are divided by the number of caller streams among the last larger calls, and
+the same results whatever the form."""
 import numpy as np
 import pytest
 import torch
 
-from gpu_util import announce, host_dict
+from gpu_util import announce, host_dict, settle
 from oracle import oracle as O
 from paper_2510_25938_amd import lj
 from paper_2510_25938_amd.inputs import random_starts
@@ -25,25 +25,45 @@ def cus():
     return torch.cuda.get_device_properties(0).multi_processor_count
 
 
-def test_helper_limits():
-    c, side = cus(), torch.cuda.Stream()
-    for n, count, pair, cls, alone, beside in [
-            (38, 8, "lj", 0, FOUR, FOUR), (38, c // 2, "lj", 0, FOUR, FOUR),
-            (38, c // 2 + 1, "lj", 0, FOUR, TWO), (38, c, "lj", 0, FOUR, TWO),
-            (38, c + 1, "lj", 0, FOUR, 0), (38, 2 * c, "lj", 0, FOUR, 0),
-            (38, 2 * c + 1, "lj", 0, TWO, 0), (38, 4 * c, "lj", 0, TWO, 0),
-            (38, 4 * c + 1, "lj", 0, 4, 4),
-            (38, c // 2, "morse", 0, FOUR, FOUR), (38, c // 2 + 1, "morse", 0, FOUR, 0),
-            (38, 2 * c + 1, "morse", 0, 0, 0),
-            (98, c // 4, "lj", 1, FOUR, FOUR), (98, c // 4 + 1, "lj", 1, FOUR, 0),
-            (98, c, "lj", 1, FOUR, 0), (98, c + 1, "lj", 1, 0, 0), (98, 4 * c, "lj", 1, DENSE, DENSE),
-            (19, 8, "lj", 0, 0, 0), (13, 8, "lj", 0, 1, 1)]:
-        b = batch(n, count, pair)
-        assert lj.minimize_forms(b, "fp64")[cls] == alone, (n, count, pair)
-        assert lj.minimize_forms(b, "fp64", stream=side)[cls] == beside, (n, count, pair)
-        mixed = lj.minimize_forms(b, "mixed")
-        assert mixed == lj.minimize_forms(b, "mixed", stream=side) and FOUR not in mixed
+@pytest.mark.parametrize("streams", [1, 2, 3, 5])
+def test_helper_limits(streams):
+    c, calls = cus(), min(streams, 4)
+    side = [None] + [torch.cuda.Stream() for _ in range(streams - 1)]
+    settle(*side)
+    for n, pair, cls, form, limit, beyond in [
+            (38, "lj", 0, FOUR, 2 * c, TWO), (38, "lj", 0, TWO, 4 * c, None),
+            (38, "morse", 0, FOUR, 2 * c, 0), (98, "lj", 1, FOUR, c, None)]:
+        for count in (1, limit // 4, limit // calls):
+            if form == TWO and count * calls <= 2 * c:
+                continue
+            for stream in side:
+                assert lj.minimize_forms(batch(n, count, pair), "fp64", stream)[cls] == form
+        over = lj.minimize_forms(batch(n, limit // calls + 1, pair), "fp64")[cls]
+        assert over == beyond or (beyond is None and over not in (FOUR, TWO))
+    for n, count, pair, cls, form in [(98, 4 * c, "lj", 1, DENSE), (38, 4 * c + 1, "lj", 0, 4),
+                                      (19, 8, "lj", 0, 0), (13, 8, "lj", 0, 1)]:
+        assert lj.minimize_forms(batch(n, count, pair), "fp64")[cls] == form
+        assert not {FOUR, TWO} & set(lj.minimize_forms(batch(n, count, pair), "mixed"))
     assert lj.minimize_forms(batch(98, 8), "fp64")[2:] == [-1, -1]
+
+
+def test_the_rule_forgets_other_streams():
+    """One caller on a stream of its own has the limits of one call; one call, and
+    small calls, on other streams are not counted."""
+    c, side, b = cus(), torch.cuda.Stream(), batch(38, 2 * cus())
+    settle(None, side)
+    assert lj.minimize_forms(b, "fp64", side)[0] == TWO
+    settle(side)
+    assert lj.minimize_forms(b, "fp64", side)[0] == FOUR
+    off, x = random_starts([2] * (c // 4 + 1), 1)
+    lj.minimize(lj.ClusterBatch(off), torch.from_numpy(x).cuda(), None, "fp64")
+    assert lj.minimize_forms(b, "fp64", side)[0] == FOUR
+    off, x = random_starts([2] * (c // 4), 1)
+    few = lj.ClusterBatch(off)
+    for _ in range(8):
+        lj.minimize(few, torch.from_numpy(x).cuda(), None, "fp64")
+    torch.cuda.synchronize()
+    assert lj.minimize_forms(b, "fp64", side)[0] == FOUR
 
 
 def test_small_and_uneven_clusters_take_two_wavefronts():
@@ -53,6 +73,7 @@ def test_small_and_uneven_clusters_take_two_wavefronts():
         off = np.concatenate([[0], np.cumsum(sizes)])
         return lj.minimize_forms(lj.ClusterBatch(off), "fp64")[0]
 
+    settle(None)
     c = cus()
     for count in (8, c, 2 * c):
         assert form([20] * count) == form([27] * count) == TWO
@@ -61,13 +82,15 @@ def test_small_and_uneven_clusters_take_two_wavefronts():
         assert form([13] * (count - 1) + [19]) == 0
 
 
-@pytest.mark.parametrize("sizes", [[20] * 5 + [27, 21, 26], [13] * 300 + [31, 2, 0, 1], [24] * 500],
-                         ids=["20to27", "13and31", "24"])
-def test_two_wavefronts_for_small_clusters_bitwise(sizes):
+@pytest.mark.parametrize("sizes", [[20] * 5 + [27, 21, 26], [13] * 300 + [31, 2, 0, 1], [24] * 500,
+                                   list(range(65)) + [20, 38, 45, 64] * 120],
+                         ids=["20to27", "13and31", "24", "0to64"])
+def test_two_wavefronts_bitwise(sizes):
     off, x = random_starts(sizes, 9995)
     b = lj.ClusterBatch(off)
     p = lj.lbfgs_params()
-    announce(f"two wavefronts small clusters={b.num} max_n={b.max_n}")
+    announce(f"two wavefronts clusters={b.num} max_n={b.max_n}")
+    settle(None)
     assert lj.minimize_forms(b, "fp64")[0] == TWO
     r = host_dict(lj.minimize(b, torch.from_numpy(x).cuda(), p, "fp64"))
     ro = O.minimize(off, x, oracle_params(p))
@@ -77,15 +100,41 @@ def test_two_wavefronts_for_small_clusters_bitwise(sizes):
 
 @pytest.mark.parametrize("n,share,pair", [(38, 1.2, "lj"), (38, 3, "lj"), (98, 0.4, "lj"),
                                           (38, 0.8, "morse")])
-def test_same_results_on_either_kind_of_stream(n, share, pair):
-    count, side = int(share * cus()), torch.cuda.Stream()
+def test_same_results_beside_other_calls(n, share, pair):
+    count, side = int(share * cus()), [torch.cuda.Stream() for _ in range(4)]
     off, x = random_starts([n] * count, 9990 + n)
     b = lj.ClusterBatch(off, pair=pair)
     xd = torch.from_numpy(x).cuda()
     p = lj.lbfgs_params(max_iter=60)
     announce(f"forms {pair}{n} x {count}")
-    assert lj.minimize_forms(b, "fp64") != lj.minimize_forms(b, "fp64", stream=side)
-    alone = host_dict(lj.minimize(b, xd, p, "fp64"))
-    beside = host_dict(lj.minimize(b, xd, p, "fp64", stream=side))
-    for key in KEYS:
-        assert np.array_equal(alone[key], beside[key]), key
+    settle(side[0])
+    form = lj.minimize_forms(b, "fp64", side[0])
+    alone = host_dict(lj.minimize(b, xd, p, "fp64", stream=side[0]))
+    settle(*side)
+    assert lj.minimize_forms(b, "fp64", side[0]) != form
+    for out in [lj.minimize(b, xd, p, "fp64", stream=s) for s in side]:
+        beside = host_dict(out)
+        for key in KEYS:
+            assert np.array_equal(alone[key], beside[key]), key
+
+
+def test_chains_beside_other_calls_keep_their_trace():
+    """Basin-hopping steps whose candidates change form between calls."""
+    off, x = random_starts([38] * 40, 9996)
+    b = lj.ClusterBatch(off)
+    p = lj.lbfgs_params()
+    r = lj.minimize(b, torch.from_numpy(x).cuda(), p, "fp64")
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    announce("chains beside other calls")
+    traces = []
+    for beside in (False, True):
+        bh = lj.BasinHopping(b, r["xyz"], r["energy"], lj.bh_params(cands=8, seed=7), p, "fp64",
+                             trace_steps=4)
+        settle(streams[0])
+        bh.step(2, stream=streams[0])
+        settle(*(streams if beside else streams[:1]))
+        bh.step(2, stream=streams[0])
+        torch.cuda.synchronize()
+        traces.append((bh.trace["e_trial"].cpu().numpy(), bh.xyz_cur.cpu().numpy()))
+    for u, v in zip(*traces):
+        assert np.array_equal(u, v)
