@@ -11,8 +11,8 @@
 //   FP32   one wavefront per pair of 64-atom tiles (split32_kernel), whose FP32
 //          partial sums are independent, then per tile their FP64 sums in
 //          order (split32_sum_kernel), then the energies as above.
-// 3 x LJ3000: FP64 2118 -> 96 us, FP32 1339 -> 41 us; one LJ1000: 189 -> 36 us
-// and 85 -> 21 us; 4 x Morse1000: 596 -> 67 us and 171 -> 21 us.
+// One workgroup per cluster -> spread, us: 3 x LJ3000 FP64 2157 -> 94, FP32
+// 1284 -> 39; 8 x LJ1000 188 -> 35 and 84 -> 17; 8 x Morse1000 396 -> 56 and 177 -> 19.
 #include <hip/hip_runtime.h>
 
 #include "lj_lbfgs.hpp"
