@@ -252,6 +252,7 @@ std::vector<RecentCalls> g_recent;  // per device
 // note: the call of num clusters is about to be enqueued on st.  A call under
 // capture says nothing of when it will run: it is taken to be alone.
 int calls_at_once(hipStream_t st, int64_t num, int cus, bool note) {
+    if (4 * num <= cus) return 1;  // within a quarter of every limit
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 1;
@@ -260,7 +261,7 @@ int calls_at_once(hipStream_t st, int64_t num, int cus, bool note) {
     std::lock_guard<std::mutex> lk(g_recent_mu);
     if ((int)g_recent.size() <= dev) g_recent.resize(dev + 1);
     RecentCalls& r = g_recent[dev];
-    if (note && 4 * num > cus) {
+    if (note) {
         r.stream[r.at] = st;
         r.at = (r.at + 1) % kRecentCalls;
         r.count = std::min(r.count + 1, kRecentCalls);
