@@ -137,31 +137,20 @@ __device__ __forceinline__ double split_pass(SplitLds& lds, int n, int tile, int
     return sum;
 }
 
-// The tile of an FP64 workgroup.  The first num nt workgroups (nt: tiles of a
-// cluster of max_n atoms) take the clusters' tiles in order; those from nt on,
-// which only a cluster above max_n has, come last.  Workgroups go to the eight
-// XCDs in turn, so with nt_max (a power of two) of them per cluster in order the
-// empty ones of every cluster fell to the same XCDs: 102 x LJ300, 5 of 8 tiles,
-// 26 us now and 46 so, 93 x LJ700 93 and 132.  The FP32 path's workgroups, many
-// per cluster or short, gain nothing by it.
-struct SplitTile {
-    int b, tile;
-};
-__device__ __forceinline__ SplitTile split_tile(int num, int nt, int nt_max) {
-    const int i = blockIdx.x, first = num * nt, rest = nt_max - nt;
-    return i < first ? SplitTile{i / nt, i % nt}
-                     : SplitTile{(i - first) / rest, nt + (i - first) % rest};
-}
-
+// Workgroup (x, b, z) takes tile x + z nt of cluster b: first the tiles that clusters
+// up to max_n have (nt of them, z = 0), then those that only a cluster above
+// max_n has (z = 1).  Workgroups go to the eight XCDs in turn, so with nt_max (a power
+// of two) of them per cluster in order the empty ones of every cluster fell to
+// the same XCDs: 102 x LJ300, 5 of 8 tiles, 26 us now and 46 so, 93 x LJ700 93 and
+// 132.  The FP32 path's workgroups, many per cluster or short, gain nothing by it.
 template <int POT>
 __global__ __launch_bounds__(kSplitBlock) void split64_kernel(const int32_t* offset, int64_t total,
                                                               const double* xyz, double* grad,
-                                                              double* partial, int num, int nt,
-                                                              int nt_max, double rho, Units u) {
+                                                              double* partial, int nt_max,
+                                                              double rho, Units u) {
     __shared__ SplitLds lds;
     __shared__ int again;
-    const SplitTile at = split_tile(num, nt, nt_max);
-    const int b = at.b, tile = at.tile;
+    const int b = blockIdx.y, tile = blockIdx.x + blockIdx.z * gridDim.x;
     const int o = offset[b], n = offset[b + 1] - o;
     if (n <= tile * kWave || n > nt_max * kWave) return;  // (the second: reported as NaN)
     const int lane = threadIdx.x % kWave, wave = uniform((int)threadIdx.x / kWave);
@@ -385,8 +374,10 @@ static hipError_t launch_split_t(int mixed, int num, int max_n, const int32_t* o
     const int nt_max = s.W * s.A, nt = (max_n + kWave - 1) / kWave;  // max_n > 256
     double* partial = reinterpret_cast<double*>(ws);
     if (!mixed) {
-        hipLaunchKernelGGL((split64_kernel<POT>), dim3(num * nt_max), dim3(kSplitBlock), 0, st, off,
-                           total, xyz, grad, partial, num, nt, nt_max, rho, u);
+        // nt <= nt_max < 2 nt, and the rule keeps num below 65536
+        hipLaunchKernelGGL((split64_kernel<POT>), dim3(nt, num, nt < nt_max ? 2 : 1),
+                           dim3(kSplitBlock), 0, st, off, total, xyz, grad, partial, nt_max, rho,
+                           u);
     } else {
         const int units = split_units(POT, nt_max);
         char* p = ws + align256((size_t)num * nt_max * sizeof(double));
