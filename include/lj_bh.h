@@ -208,9 +208,8 @@ lj_status lj_bh_minimize_batch(const lj_batch* batch, double* xyz, double* energ
  * number of LJ_SCHED_MIN_CLASS0..2 or LJ_SCHED_MIN_LARGE; + 32 for the form of
  * classes 1 and 2 with two wavefronts per SIMD; 16 or 17 for one cluster per four
  * or two wavefronts, which only the built-in rule takes (LJ_FP64, calls of few
- * clusters; fewer where the last eight larger calls of minimisations and
- * basin-hopping steps on the device came on several streams, as calls that run
- * beside one another want those SIMDs); -1 for the classes above.
+ * clusters; fewer where the last eight larger minimisations on the device came
+ * on several streams, as calls that run beside one another want those SIMDs); -1 for the classes above.
  */
 lj_status lj_minimize_forms(const lj_batch* batch, int32_t precision, void* stream,
                             int32_t* forms);

@@ -226,11 +226,13 @@ std::array<int, 4> class_key(int precision, int c, int max_n) {
 }
 
 // The calls that the built-in rule expects beside one another on the device: the
-// caller streams that made two or more of the last eight larger calls (or four,
-// the device's hardware queues, where four or more streams made them).  One call
-// on another stream, as a minimisation ahead of basin-hopping steps, does not
-// count.  Helper wavefronts take SIMDs that a call by itself leaves idle
-// but that calls on other streams would fill, so their limits are divided by
+// caller streams that made two or more of the last eight larger minimisations (or
+// four, the device's hardware queues, where four or more streams made them).  One
+// call on another stream does not count.  Basin-hopping steps run on a stream
+// because the null stream cannot be captured, often one per chain set and in turn,
+// and chains are batched into one call: they are taken to be alone.  Helper
+// wavefronts take SIMDs that a call by itself leaves idle but that calls on other
+// streams would fill, so their limits are divided by
 // that number; calls of up to a quarter of the CUs fit beside three like them and
 // are not counted.  Only a choice among forms with the same results depends on it.
 // Measured, ms for 1, 2 and 4 calls at once, without / with helper wavefronts: 1024 x
@@ -251,8 +253,8 @@ std::vector<RecentCalls> g_recent;  // per device
 
 // note: the call of num clusters is about to be enqueued on st.  A call under
 // capture says nothing of when it will run: it is taken to be alone.
-int calls_at_once(hipStream_t st, int64_t num, int cus, bool note) {
-    if (4 * num <= cus) return 1;  // within a quarter of every limit
+int calls_at_once(hipStream_t st, int num, int cus, bool note) {
+    if (num <= cus / 4) return 1;  // within a quarter of every limit
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 1;
@@ -580,7 +582,7 @@ struct BhLayout {
     int cand_num = 0;
 };
 
-lj_status bh_layout(const lj_batch* ch, const lj_bh_params* bh, int mixed, int calls, BhLayout& L) {
+lj_status bh_layout(const lj_batch* ch, const lj_bh_params* bh, int mixed, BhLayout& L) {
     const int n = bh->cands;
     L.cand_num = ch->num * n;
     L.cand_total = ch->total_atoms * n;
@@ -604,10 +606,9 @@ lj_status bh_layout(const lj_batch* ch, const lj_bh_params* bh, int mixed, int c
     L.pi = take(sizeof(int32_t) * (size_t)ch->num);
     L.pv = take(sizeof(int32_t) * (size_t)ch->num);
     L.ps = take(sizeof(int32_t) * (size_t)ch->num);
-    lj_status s = min_layout(L.cand_num, ch->max_n, L.cand_total, mixed, ch->pair, calls,
-                             L.cand_min);
+    lj_status s = min_layout(L.cand_num, ch->max_n, L.cand_total, mixed, ch->pair, 1, L.cand_min);
     if (s != LJ_OK) return s;
-    s = min_layout(ch->num, ch->max_n, ch->total_atoms, 0, ch->pair, calls, L.polish_min);
+    s = min_layout(ch->num, ch->max_n, ch->total_atoms, 0, ch->pair, 1, L.polish_min);
     if (s != LJ_OK) return s;
     L.min = off;
     const size_t m = L.cand_min.total > L.polish_min.total ? L.cand_min.total : L.polish_min.total;
@@ -968,7 +969,7 @@ size_t lj_bh_workspace_bytes(const lj_batch* chains, const lj_bh_params* bh,
     if (check_batch(chains, LJ_MAX_ATOMS_MIN, "lj_bh_workspace_bytes") != LJ_OK) return 0;
     if (check_bh(chains, bh) != LJ_OK) return 0;
     BhLayout L;
-    if (bh_layout(chains, bh, precision == LJ_MIXED, 1, L) != LJ_OK) return 0;
+    if (bh_layout(chains, bh, precision == LJ_MIXED, L) != LJ_OK) return 0;
     return L.total;
 }
 
@@ -991,11 +992,7 @@ lj_status lj_bh_step(const lj_batch* chains, const lj_bh_state* state, const lj_
     if (trace && trace->capacity_steps < 0) return fail(LJ_E_ARG, "trace capacity < 0");
     const int mixed = precision == LJ_MIXED;
     BhLayout L;
-    DeviceInfo di;
-    if ((s = device_info(di)) != LJ_OK) return s;
-    const int calls = calls_at_once(static_cast<hipStream_t>(stream),
-                                    (int64_t)chains->num * bh->cands, di.cus, true);
-    if ((s = bh_layout(chains, bh, mixed, calls, L)) != LJ_OK) return s;
+    if ((s = bh_layout(chains, bh, mixed, L)) != LJ_OK) return s;
     if (!ws || ws_bytes < L.total)
         return fail(LJ_E_WORKSPACE, "workspace of %zu bytes given, %zu needed", ws_bytes, L.total);
 

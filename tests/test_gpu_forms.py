@@ -116,25 +116,3 @@ def test_same_results_beside_other_calls(n, share, pair):
         beside = host_dict(out)
         for key in KEYS:
             assert np.array_equal(alone[key], beside[key]), key
-
-
-def test_chains_beside_other_calls_keep_their_trace():
-    """Basin-hopping steps whose candidates change form between calls."""
-    off, x = random_starts([38] * 40, 9996)
-    b = lj.ClusterBatch(off)
-    p = lj.lbfgs_params()
-    r = lj.minimize(b, torch.from_numpy(x).cuda(), p, "fp64")
-    streams = [torch.cuda.Stream() for _ in range(4)]
-    announce("chains beside other calls")
-    traces = []
-    for beside in (False, True):
-        bh = lj.BasinHopping(b, r["xyz"], r["energy"], lj.bh_params(cands=8, seed=7), p, "fp64",
-                             trace_steps=4)
-        settle(streams[0])
-        bh.step(2, stream=streams[0])
-        settle(*(streams if beside else streams[:1]))
-        bh.step(2, stream=streams[0])
-        torch.cuda.synchronize()
-        traces.append((bh.trace["e_trial"].cpu().numpy(), bh.xyz_cur.cpu().numpy()))
-    for u, v in zip(*traces):
-        assert np.array_equal(u, v)
